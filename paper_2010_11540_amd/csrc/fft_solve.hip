@@ -449,9 +449,8 @@ __device__ __forceinline__ void cols_body(const cx<T> *__restrict__ at, int nx, 
         vs[r] = k < mx ? sx[k] : T(0);
         // zero-padded column (open boundary), or its odd extension about
         // the walls at i = 0 and i = nx (grounded pipe)
-        const int src = k < nx ? k : mx - k;
-        const bool zero = pipe ? (k == 0 || k == nx) : k >= nx;
-        const cx<T> c = zero ? cx<T>{T(0), T(0)} : col[src];
+        const int src = column_source(k, nx, mx, pipe);
+        const cx<T> c = src < 0 ? cx<T>{T(0), T(0)} : col[src];
         va[r] = (pipe && k > nx) ? cx<T>{-c.re, -c.im} : c;
     }
     const T syl = sy[l];

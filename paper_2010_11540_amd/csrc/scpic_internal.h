@@ -122,6 +122,18 @@ inline int stage_twiddle_exponent(int e, int L, int log2L)
     return m * (L / (4 * ns)) * k;
 }
 
+// Row of the row spectra (nx rows) that entry k of a column's mx-point input
+// is read from, or -1 for an entry that is zero: the zero-padded column (open
+// boundary), or its odd extension about the walls at k = 0 and k = nx
+// (grounded pipe, mx = 2 nx; entries k > nx take the row's negative).  Any
+// k >= 0 is accepted: the lanes of a kernel beyond mx read nothing.
+__host__ __device__ constexpr int column_source(int k, int nx, int mx, bool pipe)
+{
+    if (k >= mx) return -1;
+    if (!pipe) return k < nx ? k : -1;
+    return (k == 0 || k == nx) ? -1 : (k < nx ? k : mx - k);
+}
+
 // Most nodes of a line-density grid.
 constexpr int kMaxLineNodes = 512;
 

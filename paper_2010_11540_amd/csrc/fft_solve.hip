@@ -4,9 +4,9 @@
 // method), the centred-difference field taken in the spectrum.  Each axis is
 // padded to the power of two mx >= 2 nx (my >= 2 ny): any such length makes
 // the cyclic convolution equal the linear one on nodes -1..n.  Hand-written
-// radix-4/2 Stockham FFTs in LDS, each run by one wave, reading per-stage
-// twiddle tables and XOR-swizzled buffers so that no stage's LDS accesses
-// conflict on banks; no vendor FFT library.
+// radix-4/2 Stockham FFTs in registers, each run by (part of) one wave, their
+// exchanges between stages through XOR-swizzled LDS buffers on which no
+// stage's accesses conflict; no vendor FFT library.
 //
 // Data flow for a charge grid q (nx x ny, rows i along x; hy = my / 2):
 //   k_rows_fwd   one workgroup per row i: sum the row's partials exactly
@@ -17,23 +17,24 @@
 //   k_cols       per column l: FFT along x (length mx, zero-padded),
 //                multiply by the real Green's spectrum G^(k,l) (inverse-FFT
 //                normalisation folded in), then two inverse FFTs run by two
-//                waves at once: -i sin(2 pi k/mx)/dx * Phi (the x central
+//                groups of lanes: -i sin(2 pi k/mx)/dx * Phi (the x central
 //                difference) and Phi, scaled by -i sin(2 pi l/my)/dy (the y
-//                central difference); rows 0..nx-1 kept -> Bx, By [nx][hy+1]
+//                central difference); rows 0..nx-1 kept -> (Bx, By) [nx][hy+1]
 //   k_rows_inv   per row i: both half spectra packed as Ex + i Ey, completed
 //                by Hermitian symmetry, one inverse FFT     -> ex, ey [nx][ny]
 // Taking the differences in the spectrum keeps the large constant part of
 // the potential out of the field's rounding, which matters for the FP32 form.
-// Every kernel issues all of its global loads into registers before the
-// first LDS write, so each kernel waits for one round of memory latency.
+// Every kernel issues all of its global loads into registers before its
+// first transform, so each kernel waits for one round of memory latency.
 #include <algorithm>
+#include <type_traits>
 
 #include "scpic_internal.h"
 
-// The solve carries no bit-exactness contract (its field is compared with the
-// direct-sum solve within a tolerance, and the batched and single-beam paths
-// share this code): multiply-adds may be fused here, unlike in the pass.
-#pragma clang fp contract(fast)
+// The solve fuses the multiply-adds it names (twiddle) and no others, so the
+// batched and the single-beam kernels, whose lengths are compiled apart, give
+// the same bits.
+#pragma clang fp contract(off)
 
 namespace scpic {
 namespace {
@@ -47,10 +48,11 @@ template <typename T>
 __device__ __forceinline__ cx<T> operator+(cx<T> a, cx<T> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename T>
 __device__ __forceinline__ cx<T> operator-(cx<T> a, cx<T> b) { return {a.re - b.re, a.im - b.im}; }
+// d * w with each part one product and one fused multiply-add
 template <typename T>
-__device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b)
+__device__ __forceinline__ cx<T> twiddle(cx<T> d, cx<T> w)
 {
-    return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+    return {fma(d.re, w.re, -(d.im * w.im)), fma(d.im, w.re, d.re * w.im)};
 }
 template <typename T>
 __device__ __forceinline__ cx<T> conj(cx<T> a) { return {a.re, -a.im}; }
@@ -80,78 +82,163 @@ __device__ __forceinline__ void wave_lds_order()
 // there a stage's outputs are written 4 ns elements apart per lane.
 __device__ __forceinline__ int sw(int e) { return e ^ ((e >> 2) & 31); }
 
-// Forward DFT X[k] = sum_n x[n] exp(-2 pi i n k / L) of the sequence in LDS
-// buffer a (length L = 2^log2L), ping-ponging with buffer b, computed by ONE
-// wave: lane = 0..63 of that wave (a lane index >= L/2 takes no butterfly,
-// which lets the other waves of a workgroup call it too, as a no-op).  The
-// input must be visible to the wave when it is called (a workgroup barrier if
-// other waves wrote it); the result is visible to the same wave on return and
-// to the others after a workgroup barrier.  Stockham autosort: one radix-2
-// stage first when log2L is odd, then radix-4 stages; each stage reads
-// sub-transform inputs L/r apart, applies the twiddles exp(-2 pi i m k / (Ns r))
-// and writes the r outputs Ns apart.  st: the stage twiddles of an L-point
-// FFT (stage_twiddle_count), in LDS.
-// Returns the buffer holding X in natural order (the same in every lane).
-template <typename T>
-__device__ cx<T> *fft_wave(cx<T> *a, cx<T> *b, int L, int log2L, const cx<T> *st, int lane)
+// Forward DFT X[k] = sum_n x[n] exp(-2 pi i n k / L), L = 2^LOG2, of a
+// sequence held in registers by a group of G lanes of one wave, E elements
+// per lane: lane t (0 <= t < G) holds element t + G r in v[r], before and
+// after.  Stockham autosort: radix-4 stages after one radix-2 stage when LOG2
+// is odd; the first stage reads and the last one writes the lane's own
+// elements, and only the exchanges between stages go through LDS (buf: L
+// elements of the group's own).  One wave's LDS accesses execute in order, so
+// a transform needs no barrier and no second buffer.  Every stage multiplies
+// by the entries of the stage twiddle table (stage_twiddle_count), which each
+// lane loads into registers once for all its transforms.
+//
+// A transform is a chain of latencies, not of work: of the ~1 us a 256-point
+// FP64 transform took with every stage reading and writing LDS, most was the
+// round trip of each stage and its twiddle reads.  Held in registers, a
+// forward transform, the product with the Green's spectrum and an inverse
+// make 6 exchanges instead of 12 and need no barrier between them.  Per
+// space-charge step, FP64: 1e6 particles on 128^2 34.5 -> 31.9 us, 1e4 on 64^2
+// 19.4 -> 16.9 us, the 64-beam scan 235 -> 222 us (its column kernel 26 -> 17
+// us, row-inverse 12 -> 8 us: a wave's lanes all transform, where one wave of
+// four did), the same bits.
+//
+// 4 elements per lane (one butterfly) leave a stage's work at its least;
+// L = 512 takes 8, which 64 lanes need, and there the radix-2 stage and the
+// first radix-4 stage share the lane's elements (no exchange between them).
+// With 8 per lane for every odd LOG2 the 128-point transforms, one exchange
+// shorter but twice the instructions per stage, were no faster than in LDS.
+template <typename T, int LOG2>
+struct WaveFft {
+    static constexpr int L = 1 << LOG2;
+    static constexpr int E = LOG2 == 9 ? 8 : 4;
+    static constexpr int G = L / E;              // lanes of one transform
+    static constexpr int B = E / 4;              // radix-4 butterflies per lane and stage
+    static constexpr int C = (LOG2 & 1) ? 2 : 1;  // ns of the first radix-4 stage
+    static constexpr int kStages = LOG2 / 2;     // radix-4 stages
+    static constexpr bool kPre = C == 2 && E == 4;  // radix-2 stage with an exchange of its own
+    static constexpr int kDone = kPre ? 0 : 1;   // radix-4 stages before the first exchange
+    static_assert(G >= 1 && G <= 64, "a transform lives in one wave");
+
+    cx<T> w[kStages - kDone][B][3];  // of the stages after the first exchange
+    cx<T> w0[E == 8 ? 3 : 1];        // first radix-4 stage's k = 1 (E == 8)
+
+    __device__ __forceinline__ void load(const cx<T> *__restrict__ st, int t)
+    {
+        if constexpr (E == 8)
+#pragma unroll
+            for (int m = 0; m < 3; ++m) w0[m] = st[3 + m];
+        int ns = kDone ? 4 * C : C;
+#pragma unroll
+        for (int s = 0; s + kDone < kStages; ++s, ns *= 4)
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int k = (t + G * b) & (ns - 1);
+#pragma unroll
+                for (int m = 0; m < 3; ++m) w[s][b][m] = st[ns - C + 3 * k + m];
+            }
+    }
+
+    static __device__ __forceinline__ void butterfly(cx<T> &a0, cx<T> &a1, cx<T> &a2, cx<T> &a3)
+    {
+        const cx<T> t0 = a0 + a2, t1 = a0 - a2, t2 = a1 + a3, t3 = a1 - a3;
+        a0 = t0 + t2;
+        a1 = t1 + mul_neg_i(t3);
+        a2 = t0 - t2;
+        a3 = t1 + mul_pos_i(t3);
+    }
+
+    __device__ __forceinline__ void run(cx<T> (&v)[E], cx<T> *buf, int t) const
+    {
+        // the stages before the first exchange, on the lane's own elements
+        if constexpr (E == 8) {
+            cx<T> p[4], q[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                p[r] = v[r] + v[r + 4];
+                q[r] = v[r] - v[r + 4];
+            }
+            // radix-4 butterflies 2 t (k = 0) and 2 t + 1 (k = 1); together
+            // their outputs are elements 8 t .. 8 t + 7
+            butterfly(p[0], p[1], p[2], p[3]);
+#pragma unroll
+            for (int m = 0; m < 3; ++m) q[m + 1] = twiddle(q[m + 1], w0[m]);
+            butterfly(q[0], q[1], q[2], q[3]);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                buf[sw(8 * t + 2 * m)] = p[m];
+                buf[sw(8 * t + 2 * m + 1)] = q[m];
+            }
+        } else if constexpr (kPre) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int e = 2 * (t + G * r);
+                buf[sw(e)] = v[r] + v[r + 2];
+                buf[sw(e + 1)] = v[r] - v[r + 2];
+            }
+        } else {
+            butterfly(v[0], v[1], v[2], v[3]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) buf[sw(4 * t + r)] = v[r];
+        }
+        int ns = kDone ? 4 * C : C;
+#pragma unroll
+        for (int s = 0; s + kDone < kStages; ++s, ns *= 4) {
+            wave_lds_order();
+#pragma unroll
+            for (int r = 0; r < E; ++r) v[r] = buf[sw(t + G * r)];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                // butterfly j = t + G b reads elements j + m L / 4 = t + G (b + B m)
+#pragma unroll
+                for (int m = 1; m < 4; ++m) v[b + B * m] = twiddle(v[b + B * m], w[s][b][m - 1]);
+                butterfly(v[b], v[b + B], v[b + 2 * B], v[b + 3 * B]);
+            }
+            if (s + kDone + 1 < kStages) {
+                wave_lds_order();
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    const int j = t + G * b, k = j & (ns - 1), base = (j - k) * 4 + k;
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) buf[sw(base + m * ns)] = v[b + B * m];
+                }
+            }
+        }
+        // the last stage's output j + m L / 4 is element t + G (b + B m): the
+        // lane's own again.  The next transform may use buf at once.
+        wave_lds_order();
+    }
+};
+
+// Calls f(std::integral_constant<int, log2>), LO <= log2 <= HI.
+template <int LO, int HI, typename F>
+__host__ __device__ __forceinline__ void with_log2(int log2, F &&f)
 {
-    int ns = 1;
-    if (log2L & 1) {
-        const int h = L >> 1;
-        for (int j = lane; j < h; j += 64) {
-            const cx<T> u = a[sw(j)], v = a[sw(j + h)];
-            b[sw(2 * j)] = u + v;
-            b[sw(2 * j + 1)] = u - v;
-        }
-        cx<T> *t = a;
-        a = b;
-        b = t;
-        ns = 2;
-        wave_lds_order();
+    if constexpr (LO < HI) {
+        if (log2 == LO)
+            f(std::integral_constant<int, LO>{});
+        else
+            with_log2<LO + 1, HI>(log2, f);
+    } else {
+        f(std::integral_constant<int, HI>{});
     }
-    const int c = ns;
-    const int q = L >> 2;
-    while (ns < L) {
-        const cx<T> *ws = st + (ns - c);
-        for (int j = lane; j < q; j += 64) {
-            const int k = j & (ns - 1);
-            const cx<T> *w = ws + 3 * k;
-            const cx<T> a0 = a[sw(j)];
-            const cx<T> a1 = cmul(a[sw(j + q)], w[0]);
-            const cx<T> a2 = cmul(a[sw(j + 2 * q)], w[1]);
-            const cx<T> a3 = cmul(a[sw(j + 3 * q)], w[2]);
-            const cx<T> t0 = a0 + a2, t1 = a0 - a2, t2 = a1 + a3, t3 = a1 - a3;
-            const int base = (j - k) * 4 + k;
-            b[sw(base)] = t0 + t2;
-            b[sw(base + ns)] = t1 + mul_neg_i(t3);
-            b[sw(base + 2 * ns)] = t0 - t2;
-            b[sw(base + 3 * ns)] = t1 + mul_pos_i(t3);
-        }
-        cx<T> *t = a;
-        a = b;
-        b = t;
-        ns *= 4;
-        wave_lds_order();
-    }
-    return a;
 }
 
-constexpr int kRowThreads = 1024;  // row-forward: 16 waves share the reduction
-constexpr int kColThreads = 256;   // columns: 4 waves; waves 0 and 1 run the inverse transforms
-constexpr int kInvThreads = 256;   // row-inverse: loads and stores over 4 waves
-constexpr int kMaxPerThread = kMaxFft / 64;
+constexpr int kRowThreads = 1024;   // row-forward: 16 waves share the reduction
+constexpr int kLineThreads = 256;   // batched column and row-inverse kernels
 
 // Exact sum of grid row i over the partials of nblocks workgroups plus the
 // carry grid (which is cleared), for the ny cells of the row.  Called by all
 // NT threads of the workgroup (NT >= ny).  Thread t reads 16-byte chunks (4 cells) of the row:
-// ny/4 lanes cover one workgroup's row segment and the kRowThreads/(ny/4)
-// groups of lanes split the workgroups, each issuing all of its loads before
-// adding any (one round of memory latency for <= kReduceChunk workgroups per
-// lane).  Chunks outside a workgroup's bounding box are not read (their
-// loads return zeros without touching memory).  hdr: the headers staged in LDS; red: LDS
-// scratch of NT * 4 uint64; carry_v: this cell's carry, loaded by
-// the caller with its first round of loads (cleared here when nonzero).
-// Returns the total of cell tid (tid < ny).
+// ny/4 lanes cover one workgroup's row segment and the NT/(ny/4) groups of
+// lanes split the workgroups.  Each lane reads the headers of its workgroups
+// itself (a group's lanes the same ones), then issues all of its chunk loads
+// before adding any: two rounds of memory latency for <= kReduceChunk
+// workgroups per lane, and no barrier between them.  Chunks outside a
+// workgroup's bounding box are not read (their loads return zeros without
+// touching memory).  red: LDS scratch of NT * 4 uint64; carry_v: this cell's
+// carry, loaded by the caller with its first round of loads (cleared here
+// when nonzero).  Returns the total of cell tid (tid < ny).
 constexpr int kReduceChunk = 8;
 
 // Lane layout of a row reduction by NT threads: lanes = ny/4 16-byte chunks
@@ -173,7 +260,6 @@ __device__ __forceinline__ RowLanes row_lanes(int ny, int tid)
 
 template <int NT>
 __device__ __forceinline__ unsigned long long reduce_row(const DepositTarget &dep,
-                                                         const BlockHeader *hdr,
                                                          unsigned long long *red, int nblocks,
                                                          int i, int ny, int tid,
                                                          unsigned long long carry_v)
@@ -194,13 +280,19 @@ __device__ __forceinline__ unsigned long long reduce_row(const DepositTarget &de
     const uint32_t row0 = (uint32_t)(sizeof(uint32_t) * ((size_t)i * dep.max_blocks * ny + j0c));
     unsigned long long s0 = 0, s1 = 0, s2 = 0, s3 = 0;
     for (int b0 = member ? grp : nblocks; b0 < nblocks; b0 += groups * kReduceChunk) {
+        uint2 box[kReduceChunk];  // rows, cols of the header
+#pragma unroll
+        for (int u = 0; u < kReduceChunk; ++u) {
+            const int b = b0 + u * groups;
+            box[u] = *reinterpret_cast<const uint2 *>(&dep.header[b < nblocks ? b : 0].rows);
+        }
         uint32_t off[kReduceChunk];
 #pragma unroll
         for (int u = 0; u < kReduceChunk; ++u) {
             const int b = b0 + u * groups;
-            const BlockHeader h = hdr[b < nblocks ? b : 0];
-            const bool take = b < nblocks && i >= h.i0 && i <= h.i1 && j0c + 3 >= h.j0 &&
-                              j0c <= h.j1;
+            const bool take = b < nblocks && i >= (int)(box[u].x & 0xffffu) &&
+                              i <= (int)(box[u].x >> 16) &&
+                              j0c + 3 >= (int)(box[u].y & 0xffffu) && j0c <= (int)(box[u].y >> 16);
             off[u] = take ? row0 + (uint32_t)(sizeof(uint32_t) * (size_t)b * ny) : kOutside;
         }
         // every load in flight before the first add
@@ -226,6 +318,7 @@ __device__ __forceinline__ unsigned long long reduce_row(const DepositTarget &de
     __syncthreads();
     unsigned long long t = 0;
     if (tid < ny) {
+#pragma unroll 8
         for (int g = 0; g < groups; ++g) t += red[(size_t)g * ny + tid];
         t += carry_v;
         if (carry_v) dep.carry[(size_t)i * ny + tid] = 0ull;
@@ -238,17 +331,14 @@ __global__ void __launch_bounds__(kRowThreads)
     k_reduce(DepositTarget dep, int nblocks, int nx, int ny, int64_t *__restrict__ q,
              int64_t *__restrict__ n_in)
 {
-    __shared__ BlockHeader hdr[kMaxPassBlocks];
     __shared__ unsigned long long red[kRowThreads * 4];
     const int tid = threadIdx.x, i = blockIdx.x;
     const unsigned long long cv = tid < ny ? dep.carry[(size_t)i * ny + tid] : 0ull;
-    for (int b = tid; b < nblocks; b += kRowThreads) hdr[b] = dep.header[b];
-    __syncthreads();
-    const unsigned long long t = reduce_row<kRowThreads>(dep, hdr, red, nblocks, i, ny, tid, cv);
+    const unsigned long long t = reduce_row<kRowThreads>(dep, red, nblocks, i, ny, tid, cv);
     if (tid < ny) q[(size_t)i * ny + tid] = (int64_t)t;
     if (n_in != nullptr && i == 0 && tid < 64) {
         long long cnt = 0;
-        for (int b = tid; b < nblocks; b += 64) cnt += hdr[b].count;
+        for (int b = tid; b < nblocks; b += 64) cnt += dep.header[b].count;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
         if (tid == 0) *n_in = cnt;
@@ -260,44 +350,40 @@ __global__ void __launch_bounds__(kRowThreads)
 // (zero from index ny on), Z = FFT_hy(z), then
 //   X[l] = (Z[l] + conj Z[hy-l]) / 2 - i W^l (Z[l] - conj Z[hy-l]) / 2,
 // W = exp(-2 pi i / my), for l = 0..hy.  tw: W^l for l = 0..hy, then the
-// stage twiddles of the hy-point FFT (the grid's stw_y table).
-// LDS of the row-forward workgroup: the twiddles W^l, l = 0..hy, the stage
-// twiddles of the hy-point FFT [hy], two FFT buffers [hy], rho [ny], then
-// (16-byte aligned) the staged headers.
+// stage twiddles of the hy-point FFT (the grid's stw_y table).  The first
+// lanes of wave 0 transform; hy = 2^LOG2.
+// The twiddles wait in LDS while the partials are summed (in the transforming
+// lanes' registers they would halve the waves that do the summing).
+// LDS of the row-forward workgroup: W^l, l = 0..hy, the stage twiddles [hy],
+// the FFT buffer [hy] and rho [ny].
 template <typename T>
-__host__ __device__ constexpr size_t rows_fwd_hdr_offset(int ny, int my)
+__host__ __device__ constexpr size_t rows_fwd_lds(int ny, int my)
 {
-    return (sizeof(cx<T>) * (size_t)(2 * my + 1) + sizeof(T) * (size_t)ny + 15) & ~(size_t)15;
+    return sizeof(cx<T>) * (size_t)(my + my / 2 + 1) + sizeof(T) * (size_t)ny;
 }
 
-template <typename T, bool FROM_PARTIALS, int NT>
+template <typename T, bool FROM_PARTIALS, int NT, int LOG2>
 __device__ __forceinline__ void rows_fwd_body(const DepositTarget &dep, int nblocks,
                                               const int64_t *__restrict__ q, double scale, int nx,
-                                              int ny, int my, int log2my,
-                                              const cx<T> *__restrict__ tw, cx<T> *__restrict__ at,
-                                              int i, bool pipe)
+                                              int ny, const cx<T> *__restrict__ tw,
+                                              cx<T> *__restrict__ at, int i, bool pipe,
+                                              unsigned long long *red)
 {
-    extern __shared__ unsigned char smem_raw[];
-    const int half = my >> 1;                           // hy: complex FFT length
+    using Fft = WaveFft<T, LOG2>;
+    constexpr int half = Fft::L, my = 2 * half;  // hy: complex FFT length
+    extern __shared__ __align__(16) unsigned char smem_raw[];
     cx<T> *twl = reinterpret_cast<cx<T> *>(smem_raw);  // W^l, l = 0..hy
-    cx<T> *st = twl + half + 1;                         // stage twiddles, hy
-    cx<T> *a = st + half;                               // hy
-    cx<T> *b = a + half;                                // hy
-    T *rho = reinterpret_cast<T *>(b + half);           // ny
-    BlockHeader *hdr = reinterpret_cast<BlockHeader *>(smem_raw + rows_fwd_hdr_offset<T>(ny, my));
-    __shared__ unsigned long long red[FROM_PARTIALS ? NT * 4 : 1];
+    cx<T> *st = twl + half + 1;                        // hy
+    cx<T> *z = st + half;                              // hy
+    T *rho = reinterpret_cast<T *>(z + half);         // ny
     const int tid = threadIdx.x;
-    // one round of loads: twiddles, and the headers or the dense row (ny <= NT)
+    // one round of loads: twiddles, and the carries or the dense row (ny <= NT)
     const int64_t qv = (!FROM_PARTIALS && tid < ny) ? q[(size_t)i * ny + tid] : 0;
     const unsigned long long cv =
         (FROM_PARTIALS && tid < ny) ? dep.carry[(size_t)i * ny + tid] : 0ull;
-    // W^l for l <= hy and the hy-point FFT's stage twiddles, as stored
-    for (int t = tid; t <= half + stage_twiddle_count(half, log2my - 1); t += NT) twl[t] = tw[t];
-    if (FROM_PARTIALS)
-        for (int t = tid; t < nblocks; t += NT) hdr[t] = dep.header[t];
+    for (int e = tid; e <= half + stage_twiddle_count(half, LOG2); e += NT) twl[e] = tw[e];
     if (FROM_PARTIALS) {
-        __syncthreads();
-        const unsigned long long t = reduce_row<NT>(dep, hdr, red, nblocks, i, ny, tid, cv);
+        const unsigned long long t = reduce_row<NT>(dep, red, nblocks, i, ny, tid, cv);
         if (tid < ny) rho[tid] = (T)((double)t * scale);
     } else {
         if (tid < ny) rho[tid] = (T)((double)qv * scale);
@@ -311,16 +397,25 @@ __device__ __forceinline__ void rows_fwd_body(const DepositTarget &dep, int nblo
         if (i == 0 || l == 0 || l == ny) return T(0);
         return l < ny ? rho[l] : -rho[my - l];
     };
-    if (tid < half) a[sw(tid)] = cx<T>{sample(2 * tid), sample(2 * tid + 1)};
-    __syncthreads();
-    // wave 0 transforms; the other waves only learn where the result lies
-    const cx<T> *Z = fft_wave(a, b, half, log2my - 1, st, tid < 64 ? tid : half);
+    if (tid < Fft::G) {
+        cx<T> v[Fft::E];
+#pragma unroll
+        for (int r = 0; r < Fft::E; ++r) {
+            const int m = tid + Fft::G * r;
+            v[r] = cx<T>{sample(2 * m), sample(2 * m + 1)};
+        }
+        Fft fft;
+        fft.load(st, tid);
+        fft.run(v, z, tid);
+#pragma unroll
+        for (int r = 0; r < Fft::E; ++r) z[sw(tid + Fft::G * r)] = v[r];
+    }
     __syncthreads();
     for (int l = tid; l <= half; l += NT) {
-        const cx<T> zl = Z[sw(l & (half - 1))];
-        const cx<T> zm = conj(Z[sw((half - l) & (half - 1))]);
+        const cx<T> zl = z[sw(l & (half - 1))];
+        const cx<T> zm = conj(z[sw((half - l) & (half - 1))]);
         const cx<T> s = zl + zm, d = zl - zm;
-        const cx<T> wd = mul_neg_i(cmul(twl[l], d));
+        const cx<T> wd = mul_neg_i(twiddle(d, twl[l]));
         at[(size_t)l * nx + i] = scale_c(s + wd, T(0.5));
     }
 }
@@ -333,7 +428,7 @@ __device__ __forceinline__ void rows_fwd_body(const DepositTarget &dep, int nblo
 template <int NT>
 __device__ __forceinline__ void line_table_body(const LineSpec &L, int nblocks)
 {
-    extern __shared__ unsigned char smem_raw[];
+    extern __shared__ __align__(16) unsigned char smem_raw[];
     unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem_raw);
     __shared__ unsigned long long wmax[NT / 64];
     const int tid = threadIdx.x, nz = L.nz;
@@ -381,20 +476,21 @@ __device__ __forceinline__ void line_table_body(const LineSpec &L, int nblocks)
     }
 }
 
-// Rows of the charge grid; with a line density (line.nz > 0) one more
-// workgroup, index nx, reduces the line histograms.
-template <typename T, bool FROM_PARTIALS>
-__global__ void __launch_bounds__(kRowThreads)
+// Rows of the charge grid (LOG2: of the half length hy); with a line density
+// (line.nz > 0) one more workgroup, index nx, reduces the line histograms.
+template <typename T, bool FROM_PARTIALS, int LOG2>
+__global__ void __launch_bounds__(kRowThreads, 8)
     k_rows_fwd(DepositTarget dep, int nblocks, const int64_t *__restrict__ q, double scale,
-               int nx, int ny, int my, int log2my, const cx<T> *__restrict__ tw,
-               cx<T> *__restrict__ at, bool pipe, LineSpec line)
+               int nx, int ny, const cx<T> *__restrict__ tw, cx<T> *__restrict__ at, bool pipe,
+               LineSpec line)
 {
+    __shared__ unsigned long long red[FROM_PARTIALS ? kRowThreads * 4 : 1];
     if (line.nz > 0 && (int)blockIdx.x == nx) {
         line_table_body<kRowThreads>(line, nblocks);
         return;
     }
-    rows_fwd_body<T, FROM_PARTIALS, kRowThreads>(dep, nblocks, q, scale, nx, ny, my, log2my, tw,
-                                                 at, (int)blockIdx.x, pipe);
+    rows_fwd_body<T, FROM_PARTIALS, kRowThreads, LOG2>(dep, nblocks, q, scale, nx, ny, tw, at,
+                                                       (int)blockIdx.x, pipe, red);
 }
 
 // Every beam of a batch: workgroup -> (beam, row) from the batch's row table;
@@ -405,243 +501,263 @@ __global__ void __launch_bounds__(kRowThreads)
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT) k_rows_fwd_batched(BatchLaunch b)
 {
+    __shared__ unsigned long long red[NT * 4];
     const BatchInstance &I = b.inst[b.row_inst[blockIdx.x]];
-    rows_fwd_body<T, true, NT>(I.dep, I.pass_blocks, nullptr, I.scale, I.nx, I.ny,
-                                             I.my, I.log2_my, (const cx<T> *)I.stw_y,
-                                             (cx<T> *)I.spec_a, (int)blockIdx.x - I.row_block0,
-                                             false);
+    with_log2<3, NT == 128 ? 7 : 8>(I.log2_my - 1, [&](auto log2) {
+        rows_fwd_body<T, true, NT, decltype(log2)::value>(
+            I.dep, I.pass_blocks, nullptr, I.scale, I.nx, I.ny, (const cx<T> *)I.stw_y,
+            (cx<T> *)I.spec_a, (int)blockIdx.x - I.row_block0, false, red);
+    });
 }
 
-// Column l (of hy + 1) of the row spectra: forward FFT along x, times the
-// Green's spectrum, then the two differentiated inverse transforms, one per
-// wave.  The second is the column-inverse of the potential's spectrum before
-// the y difference (tw: the stage twiddles of the mx-point FFT); bp, when
-// not null, receives it as well for the node
+// What the column kernels read and write of one grid.
+template <typename T>
+struct ColumnArgs {
+    const cx<T> *at;  // row spectra [hy+1][nx]
+    const cx<T> *tw;  // stage twiddles of the mx-point FFT
+    const T *ghat_t, *sx, *sy;
+    cx<T> *b;         // (Bx, By) pairs [nx][hy+1]
+    cx<T> *bp;        // the potential's column-inverse spectrum, or null
+    int nx, hy;
+    bool pipe;
+};
+
+// Column l (of hy + 1) of the row spectra in one group of G lanes: forward
+// FFT along x, times the Green's spectrum, then one of the two differentiated
+// inverse transforms (dir 0: x, dir 1: y); the two groups of a column both
+// run the forward transform, which costs nothing while one of them would only
+// wait, and then no group waits for another.  The forward transform's output
+// is in the lanes that the inverse's first stage reads it in, so the product
+// stays in registers.  dir 1 also gives the column-inverse of the potential's
+// spectrum before the y difference to bp, when not null, for the node
 // potential, on rows -1..nx (row i at bp[(i + 1) * (hy + 1)]; row -1 is the
 // periodic row mx - 1, which the zero padding or the odd extension makes the
 // potential's value one node outside the grid).
-template <typename T>
-__device__ __forceinline__ void cols_body(const cx<T> *__restrict__ at, int nx, int hy, int mx,
-                                          int log2mx, const cx<T> *__restrict__ tw,
-                                          const T *__restrict__ ghat_t, const T *__restrict__ sx,
-                                          const T *__restrict__ sy, cx<T> *__restrict__ bx,
-                                          cx<T> *__restrict__ by, int l, bool pipe,
-                                          cx<T> *__restrict__ bp = nullptr)
+template <typename T, int LOG2>
+__device__ __forceinline__ void column(const ColumnArgs<T> &c, int l, int dir, int t, cx<T> *buf)
 {
-    extern __shared__ unsigned char smem_raw[];
-    cx<T> *st = reinterpret_cast<cx<T> *>(smem_raw);  // stage twiddles
-    cx<T> *a = st + mx;
-    cx<T> *b = a + mx;
-    cx<T> *c = b + mx;
-    cx<T> *d = c + mx;
-    const int tid = threadIdx.x;
-    const cx<T> *col = at + (size_t)l * nx;
-    const T *g = ghat_t + (size_t)l * mx;
-    constexpr int kPer = kMaxFft / kColThreads;
+    using Fft = WaveFft<T, LOG2>;
+    constexpr int mx = Fft::L, E = Fft::E, G = Fft::G;
+    const bool live = l <= c.hy;  // the last workgroup's spare groups store nothing
+    if (!live) l = c.hy;
+    const cx<T> *col = c.at + (size_t)l * c.nx;
+    const T *g = c.ghat_t + (size_t)l * mx;
     // every input of the column in one round of loads
-    cx<T> vt[kPer], va[kPer];
-    T vg[kPer], vs[kPer];
+    cx<T> v[E];
+    T vg[E], vs[E];
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int k = tid + r * kColThreads;
-        vt[r] = k < stage_twiddle_count(mx, log2mx) ? tw[k] : cx<T>{T(0), T(0)};
-        vg[r] = k < mx ? g[k] : T(0);
-        vs[r] = k < mx ? sx[k] : T(0);
+    for (int r = 0; r < E; ++r) {
+        const int k = t + G * r;
         // zero-padded column (open boundary), or its odd extension about
         // the walls at i = 0 and i = nx (grounded pipe)
-        const int src = column_source(k, nx, mx, pipe);
-        const cx<T> c = src < 0 ? cx<T>{T(0), T(0)} : col[src];
-        va[r] = (pipe && k > nx) ? cx<T>{-c.re, -c.im} : c;
+        const int src = column_source(k, c.nx, mx, c.pipe);
+        const cx<T> z = src < 0 ? cx<T>{T(0), T(0)} : col[src];
+        v[r] = (c.pipe && k > c.nx) ? cx<T>{-z.re, -z.im} : z;
     }
-    const T syl = sy[l];
+    Fft fft;
+    fft.load(c.tw, t);
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int k = tid + r * kColThreads;
-        if (k < mx) {
-            st[k] = vt[r];
-            a[sw(k)] = va[r];
-        }
+    for (int r = 0; r < E; ++r) {
+        vg[r] = g[t + G * r];
+        vs[r] = dir == 0 ? c.sx[t + G * r] : T(0);
     }
-    __syncthreads();
-    const cx<T> *r0 = fft_wave(a, b, mx, log2mx, st, tid < 64 ? tid : mx);
-    __syncthreads();
-    // Inverse transforms as conj(FFT(conj(.))): stage the conjugated inputs,
-    // x difference in c, y part in d.
+    const T syl = c.sy[l];
+    fft.run(v, buf, t);
+    // Inverse transforms as conj(FFT(conj(.))) of the conjugated inputs.
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int k = tid + r * kColThreads;
-        if (k < mx) {
-            const cx<T> phi = scale_c(r0[sw(k)], vg[r]);
-            c[sw(k)] = conj(mul_neg_i(scale_c(phi, vs[r])));
-            d[sw(k)] = conj(phi);
-        }
+    for (int r = 0; r < E; ++r) {
+        const cx<T> phi = scale_c(v[r], vg[r]);
+        v[r] = dir == 0 ? conj(mul_neg_i(scale_c(phi, vs[r]))) : conj(phi);
     }
-    const int wave = tid >> 6, lane = tid & 63;
-    __syncthreads();
-    // waves 0 and 1 run the two inverse transforms side by side; waves 2 and
-    // 3 only helped load and stage
-    if (wave >= 2) return;
-    cx<T> *in = wave ? d : c;
-    cx<T> *tmp = wave ? b : a;
-    const cx<T> *res = fft_wave(in, tmp, mx, log2mx, st, lane);
-    if (wave == 0) {
-        for (int i = lane; i < nx; i += 64) bx[(size_t)i * (hy + 1) + l] = conj(res[sw(i)]);
-    } else if (wave == 1) {
-        for (int i = lane; i < nx; i += 64)
-            by[(size_t)i * (hy + 1) + l] = mul_neg_i(scale_c(conj(res[sw(i)]), syl));
-        if (bp)
-            for (int i = lane - 1; i <= nx; i += 64)
-                bp[(size_t)(i + 1) * (hy + 1) + l] = conj(res[sw(i < 0 ? mx - 1 : i)]);
+    fft.run(v, buf, t);
+    if (!live) return;
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const int i = t + G * r;
+        const cx<T> u = conj(v[r]);
+        if (i < c.nx)
+            c.b[2 * ((size_t)i * (c.hy + 1) + l) + dir] =
+                dir == 0 ? u : mul_neg_i(scale_c(u, syl));
+        if (c.bp && dir == 1 && (i <= c.nx || i == mx - 1))
+            c.bp[(size_t)(i <= c.nx ? i + 1 : 0) * (c.hy + 1) + l] = u;
     }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kColThreads)
-    k_cols(const cx<T> *__restrict__ at, int nx, int hy, int mx, int log2mx,
-           const cx<T> *__restrict__ tw, const T *__restrict__ ghat_t, const T *__restrict__ sx,
-           const T *__restrict__ sy, cx<T> *__restrict__ bx, cx<T> *__restrict__ by, bool pipe,
-           cx<T> *__restrict__ bp)
+// Threads of a single-beam column workgroup: one wave when it holds a
+// column's two groups, else two.
+template <int LOG2>
+constexpr int column_threads()
 {
-    cols_body<T>(at, nx, hy, mx, log2mx, tw, ghat_t, sx, sy, bx, by, (int)blockIdx.x, pipe, bp);
+    return WaveFft<float, LOG2>::G > 32 ? 2 * WaveFft<float, LOG2>::G : 64;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kColThreads) k_cols_batched(BatchLaunch b)
+template <typename T, int LOG2>
+__global__ void __launch_bounds__(column_threads<LOG2>()) k_cols(ColumnArgs<T> c)
 {
+    using Fft = WaveFft<T, LOG2>;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int group = threadIdx.x / Fft::G;
+    constexpr int kColumns = column_threads<LOG2>() / (2 * Fft::G);
+    column<T, LOG2>(c, (int)blockIdx.x * kColumns + (group >> 1), group & 1,
+                    threadIdx.x % Fft::G,
+                    reinterpret_cast<cx<T> *>(smem_raw) + (size_t)group * Fft::L);
+}
+
+// Every beam of a batch: kLineThreads / (2 G) neighbouring columns per
+// workgroup; FFT lengths up to 2^MAXLOG.
+template <typename T, int MAXLOG>
+__global__ void __launch_bounds__(kLineThreads) k_cols_batched(BatchLaunch b)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
     const BatchInstance &I = b.inst[b.col_inst[blockIdx.x]];
-    cols_body<T>((const cx<T> *)I.spec_a, I.nx, I.my >> 1, I.mx, I.log2_mx, (const cx<T> *)I.stw_x,
-                 (const T *)I.ghat_t, (const T *)I.sx, (const T *)I.sy, (cx<T> *)I.spec_bx,
-                 (cx<T> *)I.spec_by, (int)blockIdx.x - I.col_block0, false);
+    const ColumnArgs<T> c{(const cx<T> *)I.spec_a, (const cx<T> *)I.stw_x, (const T *)I.ghat_t,
+                          (const T *)I.sx, (const T *)I.sy, (cx<T> *)I.spec_b, nullptr,
+                          I.nx, I.my >> 1, false};
+    with_log2<4, MAXLOG>(I.log2_mx, [&](auto log2) {
+        using Fft = WaveFft<T, decltype(log2)::value>;
+        const int group = threadIdx.x / Fft::G;
+        constexpr int kColumns = kLineThreads / (2 * Fft::G);
+        column<T, decltype(log2)::value>(
+            c, ((int)blockIdx.x - I.col_block0) * kColumns + (group >> 1), group & 1,
+            threadIdx.x % Fft::G, reinterpret_cast<cx<T> *>(smem_raw) + (size_t)group * Fft::L);
+    });
 }
 
-// Row i: Z[l] = Bx[l] + i By[l] for l = 0..hy and Z[my-l] = conj(Bx[l]) +
-// i conj(By[l]) for 0 < l < hy (hy = my / 2); one inverse FFT gives ex + i ey
-// on the first ny entries (tw: the stage twiddles of the my-point FFT).  Written
-// either as two arrays (ex, ey) or interleaved into ef (Ex, Ey per node).
-// With bp (the potential's column-inverse spectrum), a second inverse FFT of
-// its Hermitian row writes row i of the node potential phi on columns
-// -1..ny (phi[(i + 1) * (ny + 2) + j + 1]); rows -1 and nx (i < 0 or
-// i == nx) write only that.
-template <typename T>
-__device__ __forceinline__ void rows_inv_body(const cx<T> *__restrict__ bx,
-                                              const cx<T> *__restrict__ by, int nx, int ny, int my,
-                                              int log2my, const cx<T> *__restrict__ tw,
-                                              T *__restrict__ ex, T *__restrict__ ey,
-                                              cx<T> *__restrict__ ef, int i,
-                                              const cx<T> *__restrict__ bp = nullptr,
-                                              T *__restrict__ phi = nullptr)
+// Row i in one group of G lanes: Z[l] = Bx[l] + i By[l] for l = 0..hy and
+// Z[my-l] = conj(Bx[l]) + i conj(By[l]) for 0 < l < hy (hy = my / 2); one
+// inverse FFT gives ex + i ey on the first ny entries (tw: the stage twiddles
+// of the my-point FFT).  Written either as two arrays (ex, ey) or interleaved
+// into ef (Ex, Ey per node).
+template <typename T, int LOG2>
+__device__ __forceinline__ void field_row(const cx<T> *__restrict__ b, int nx, int ny,
+                                          const cx<T> *__restrict__ tw, T *__restrict__ ex,
+                                          T *__restrict__ ey, cx<T> *__restrict__ ef, int i, int t,
+                                          cx<T> *buf)
 {
-    extern __shared__ unsigned char smem_raw[];
-    cx<T> *st = reinterpret_cast<cx<T> *>(smem_raw);  // stage twiddles
-    cx<T> *a = st + my;
-    cx<T> *b = a + my;
-    const int tid = threadIdx.x;
-    const int hy = my >> 1;
-    // rows -1 and nx have no field: their (unused) spectrum loads read row 0
-    const int fi = (i >= 0 && i < nx) ? i : 0;
-    const cx<T> *rx = bx + (size_t)fi * (hy + 1);
-    const cx<T> *ry = by + (size_t)fi * (hy + 1);
-    constexpr int kPerT = kMaxFft / kInvThreads;          // twiddles per thread
-    constexpr int kPerL = kMaxFft / 2 / kInvThreads + 1;  // spectrum entries per thread
-    cx<T> vt[kPerT], vx[kPerL], vy[kPerL];
+    using Fft = WaveFft<T, LOG2>;
+    constexpr int my = Fft::L, hy = my / 2;
+    const bool live = i >= 0 && i < nx;  // spare groups read row 0, store nothing
+    const cx<T> *row = b + 2 * (size_t)(live ? i : 0) * (hy + 1);
+    cx<T> v[Fft::E];
 #pragma unroll
-    for (int r = 0; r < kPerT; ++r) {
-        const int t = tid + r * kInvThreads;
-        vt[r] = t < stage_twiddle_count(my, log2my) ? tw[t] : cx<T>{T(0), T(0)};
+    for (int r = 0; r < Fft::E; ++r) {
+        const int e = t + Fft::G * r, l = e <= hy ? e : my - e;
+        const cx<T> X = row[2 * l], Y = row[2 * l + 1];
+        // conjugated inputs for conj(FFT(conj(.)))
+        v[r] = e <= hy ? conj(X + mul_pos_i(Y)) : conj(conj(X) + mul_pos_i(conj(Y)));
     }
+    Fft fft;
+    fft.load(tw, t);
+    fft.run(v, buf, t);
 #pragma unroll
-    for (int r = 0; r < kPerL; ++r) {
-        const int l = tid + r * kInvThreads;
-        vx[r] = l <= hy ? rx[l] : cx<T>{T(0), T(0)};
-        vy[r] = l <= hy ? ry[l] : cx<T>{T(0), T(0)};
-    }
-#pragma unroll
-    for (int r = 0; r < kPerT; ++r) {
-        const int t = tid + r * kInvThreads;
-        if (t < my) st[t] = vt[r];
-    }
-#pragma unroll
-    for (int r = 0; r < kPerL; ++r) {
-        const int l = tid + r * kInvThreads;
-        if (l <= hy) {
-            const cx<T> X = vx[r], Y = vy[r];
-            // conjugated inputs for conj(FFT(conj(.)))
-            a[sw(l)] = conj(X + mul_pos_i(Y));
-            if (l > 0 && l < hy) a[sw(my - l)] = conj(conj(X) + mul_pos_i(conj(Y)));
-        }
-    }
-    // the potential's row (with bp) is staged beside the field's
-    cx<T> *a2 = b + my;
-    cx<T> *b2 = a2 + my;
-    if (bp) {
-        const cx<T> *rp = bp + (size_t)(i + 1) * (hy + 1);
-        for (int l = tid; l <= hy; l += kInvThreads) {
-            const cx<T> P = rp[l];
-            a2[sw(l)] = conj(P);
-            if (l > 0 && l < hy) a2[sw(my - l)] = P;
-        }
-    }
-    __syncthreads();
-    // wave 0 transforms and stores the field row, wave 1 the potential's
-    const int wave = tid >> 6, lane = tid & 63;
-    const bool field_row = i >= 0 && i < nx;
-    if (wave == 0 && field_row) {
-        const cx<T> *r = fft_wave(a, b, my, log2my, st, lane);
+    for (int r = 0; r < Fft::E; ++r) {
+        const int j = t + Fft::G * r;
+        if (!live || j >= ny) continue;
+        const cx<T> z = conj(v[r]);
         if (ef) {
-            for (int j = lane; j < ny; j += 64) ef[(size_t)i * ny + j] = conj(r[sw(j)]);
+            ef[(size_t)i * ny + j] = z;
         } else {
-            for (int j = lane; j < ny; j += 64) {
-                const cx<T> z = conj(r[sw(j)]);
-                ex[(size_t)i * ny + j] = z.re;
-                ey[(size_t)i * ny + j] = z.im;
-            }
+            ex[(size_t)i * ny + j] = z.re;
+            ey[(size_t)i * ny + j] = z.im;
         }
     }
-    if (wave == 1 && bp) {
-        const cx<T> *r2 = fft_wave(a2, b2, my, log2my, st, lane);
-        T *row = phi + (size_t)(i + 1) * (ny + 2);
-        for (int j = lane - 1; j <= ny; j += 64) row[j + 1] = r2[sw(j < 0 ? my - 1 : j)].re;
+}
+
+// Row i (-1..nx) of the node potential on columns -1..ny
+// (phi[(i + 1) * (ny + 2) + j + 1]) from the potential's column-inverse
+// spectrum: one inverse FFT of its Hermitian row.
+template <typename T, int LOG2>
+__device__ __forceinline__ void potential_row(const cx<T> *__restrict__ bp, int ny,
+                                              const cx<T> *__restrict__ tw, T *__restrict__ phi,
+                                              int i, int t, cx<T> *buf)
+{
+    using Fft = WaveFft<T, LOG2>;
+    constexpr int my = Fft::L, hy = my / 2;
+    const cx<T> *row = bp + (size_t)(i + 1) * (hy + 1);
+    cx<T> v[Fft::E];
+#pragma unroll
+    for (int r = 0; r < Fft::E; ++r) {
+        const int e = t + Fft::G * r;
+        v[r] = e <= hy ? conj(row[e]) : row[my - e];
+    }
+    Fft fft;
+    fft.load(tw, t);
+    fft.run(v, buf, t);
+    T *out = phi + (size_t)(i + 1) * (ny + 2);
+#pragma unroll
+    for (int r = 0; r < Fft::E; ++r) {
+        const int j = t + Fft::G * r;
+        if (j <= ny || j == my - 1) out[j <= ny ? j + 1 : 0] = v[r].re;
     }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kInvThreads)
-    k_rows_inv(const cx<T> *__restrict__ bx, const cx<T> *__restrict__ by, int nx, int ny, int my,
-               int log2my, const cx<T> *__restrict__ tw, T *__restrict__ ex, T *__restrict__ ey,
-               cx<T> *__restrict__ ef, const cx<T> *__restrict__ bp, T *__restrict__ phi)
+// One wave of field rows per workgroup; with the potential (bp) the last
+// nx + 2 groups of rows are the potential's rows -1..nx.
+template <typename T, int LOG2>
+__global__ void __launch_bounds__(64)
+    k_rows_inv(const cx<T> *__restrict__ b, int nx, int ny, const cx<T> *__restrict__ tw,
+               T *__restrict__ ex, T *__restrict__ ey, cx<T> *__restrict__ ef,
+               const cx<T> *__restrict__ bp, T *__restrict__ phi)
 {
-    // workgroups nx and nx + 1 (launched with the potential) take rows -1 and nx
-    const int r = (int)blockIdx.x;
-    const int i = r < nx ? r : (r == nx ? -1 : nx);
-    rows_inv_body<T>(bx, by, nx, ny, my, log2my, tw, ex, ey, ef, i, bp, phi);
+    using Fft = WaveFft<T, LOG2>;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    constexpr int kRows = 64 / Fft::G;
+    const int group = threadIdx.x / Fft::G, t = threadIdx.x % Fft::G;
+    cx<T> *buf = reinterpret_cast<cx<T> *>(smem_raw) + (size_t)group * Fft::L;
+    const int field_blocks = (nx + kRows - 1) / kRows, blk = (int)blockIdx.x;
+    if (blk < field_blocks) {
+        field_row<T, LOG2>(b, nx, ny, tw, ex, ey, ef, blk * kRows + group, t, buf);
+    } else {
+        // spare groups of the last workgroup repeat row nx
+        const int i = (blk - field_blocks) * kRows + group - 1;
+        potential_row<T, LOG2>(bp, ny, tw, phi, i < nx ? i : nx, t, buf);
+    }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kInvThreads) k_rows_inv_batched(BatchLaunch b)
+// Every beam of a batch: kLineThreads / G rows per workgroup; FFT lengths up
+// to 2^MAXLOG.
+template <typename T, int MAXLOG>
+__global__ void __launch_bounds__(kLineThreads) k_rows_inv_batched(BatchLaunch b)
 {
-    const BatchInstance &I = b.inst[b.row_inst[blockIdx.x]];
-    rows_inv_body<T>((const cx<T> *)I.spec_bx, (const cx<T> *)I.spec_by, I.nx, I.ny, I.my,
-                     I.log2_my, (const cx<T> *)I.stw_y + I.my + 1, nullptr, nullptr, (cx<T> *)I.ef,
-                     (int)blockIdx.x - I.row_block0);
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const BatchInstance &I = b.inst[b.inv_inst[blockIdx.x]];
+    with_log2<4, MAXLOG>(I.log2_my, [&](auto log2) {
+        using Fft = WaveFft<T, decltype(log2)::value>;
+        const int group = threadIdx.x / Fft::G;
+        constexpr int kRows = kLineThreads / Fft::G;
+        field_row<T, decltype(log2)::value>(
+            (const cx<T> *)I.spec_b, I.nx, I.ny, (const cx<T> *)I.stw_y + I.my + 1, nullptr,
+            nullptr, (cx<T> *)I.ef, ((int)blockIdx.x - I.inv_block0) * kRows + group,
+            threadIdx.x % Fft::G, reinterpret_cast<cx<T> *>(smem_raw) + (size_t)group * Fft::L);
+    });
 }
 
 template <typename T>
 hipError_t launch_tail(hipStream_t s, const SolveWorkspace &w, void *ex, void *ey, void *ef)
 {
     const bool want_phi = w.want_phi;
-    const size_t col_lds = 5 * sizeof(cx<T>) * (size_t)w.mx;
-    const size_t inv_lds = (want_phi ? 5 : 3) * sizeof(cx<T>) * (size_t)w.my;
-    cx<T> *bp = want_phi ? (cx<T> *)w.spec_p : nullptr;
-    hipLaunchKernelGGL(k_cols<T>, dim3(w.my / 2 + 1), dim3(kColThreads), col_lds, s,
-                       (const cx<T> *)w.spec_a, w.nx, w.my / 2, w.mx, w.log2_mx, (const cx<T> *)w.stw_x,
-                       (const T *)w.ghat_t, (const T *)w.sx, (const T *)w.sy, (cx<T> *)w.spec_bx,
-                       (cx<T> *)w.spec_by, w.pipe, bp);
+    const ColumnArgs<T> c{(const cx<T> *)w.spec_a, (const cx<T> *)w.stw_x, (const T *)w.ghat_t,
+                          (const T *)w.sx, (const T *)w.sy, (cx<T> *)w.spec_b,
+                          want_phi ? (cx<T> *)w.spec_p : nullptr, w.nx, w.my / 2, w.pipe};
+    with_log2<4, 9>(w.log2_mx, [&](auto log2) {
+        constexpr int LOG2 = decltype(log2)::value, NT = column_threads<LOG2>();
+        using Fft = WaveFft<T, LOG2>;
+        constexpr int kColumns = NT / (2 * Fft::G);
+        hipLaunchKernelGGL((k_cols<T, LOG2>), dim3((c.hy + kColumns) / kColumns), dim3(NT),
+                           sizeof(cx<T>) * NT * Fft::E, s, c);
+    });
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rows_inv<T>, dim3(w.nx + (want_phi ? 2 : 0)), dim3(kInvThreads), inv_lds, s,
-                       (const cx<T> *)w.spec_bx, (const cx<T> *)w.spec_by, w.nx, w.ny, w.my,
-                       w.log2_my, (const cx<T> *)w.stw_y + w.my + 1, (T *)ex, (T *)ey, (cx<T> *)ef,
-                       (const cx<T> *)bp, want_phi ? (T *)w.phi : (T *)nullptr);
+    with_log2<4, 9>(w.log2_my, [&](auto log2) {
+        constexpr int LOG2 = decltype(log2)::value;
+        using Fft = WaveFft<T, LOG2>;
+        constexpr int kRows = 64 / Fft::G;
+        const int blocks = (w.nx + kRows - 1) / kRows + (want_phi ? (w.nx + 1 + kRows) / kRows : 0);
+        hipLaunchKernelGGL((k_rows_inv<T, LOG2>), dim3(blocks), dim3(64),
+                           sizeof(cx<T>) * 64 * Fft::E, s, (const cx<T> *)w.spec_b,
+                           w.nx, w.ny, (const cx<T> *)w.stw_y + w.my + 1, (T *)ex, (T *)ey,
+                           (cx<T> *)ef, (const cx<T> *)c.bp, want_phi ? (T *)w.phi : (T *)nullptr);
+    });
     return hipGetLastError();
 }
 
@@ -652,48 +768,71 @@ hipError_t launch_solve_t(hipStream_t s, const SolveWorkspace &w, const DepositT
 {
     // the line tables come from the partials of a depositing pass only
     LineSpec line = FROM_PARTIALS ? w.line : LineSpec{};
-    size_t row_lds = rows_fwd_hdr_offset<T>(w.ny, w.my) +
-                     (FROM_PARTIALS ? sizeof(BlockHeader) * (size_t)std::max(nblocks, 1) : 0);
+    size_t row_lds = rows_fwd_lds<T>(w.ny, w.my);
     if (line.nz > 0) row_lds = std::max(row_lds, sizeof(unsigned long long) * (size_t)kRowThreads);
-    hipLaunchKernelGGL((k_rows_fwd<T, FROM_PARTIALS>), dim3(w.nx + (line.nz > 0 ? 1 : 0)),
-                       dim3(kRowThreads), row_lds, s, dep, nblocks, q, scale, w.nx, w.ny, w.my,
-                       w.log2_my, (const cx<T> *)w.stw_y, (cx<T> *)w.spec_a, w.pipe, line);
+    with_log2<3, 8>(w.log2_my - 1, [&](auto log2) {
+        hipLaunchKernelGGL((k_rows_fwd<T, FROM_PARTIALS, decltype(log2)::value>),
+                           dim3(w.nx + (line.nz > 0 ? 1 : 0)), dim3(kRowThreads), row_lds, s, dep,
+                           nblocks, q, scale, w.nx, w.ny, (const cx<T> *)w.stw_y,
+                           (cx<T> *)w.spec_a, w.pipe, line);
+    });
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_tail<T>(s, w, ex, ey, ef);
 }
 
+// LDS of a batched column or row-inverse workgroup: kLineThreads lanes of 4
+// elements each (8 when a beam's FFT has 512 points).  The kernels for batches
+// without such a beam leave the 512-point code, and its registers, out.
 template <typename T>
-hipError_t launch_solve_batched_t(hipStream_t s, const BatchLaunch &b, int rows, int cols,
-                                  int max_mx, int max_ny, int max_my, int max_pass_blocks)
+hipError_t launch_solve_batched_t(hipStream_t s, const BatchLaunch &b, const BatchGridShape &g)
 {
-    const int mmx = max_mx, mmy = max_my;
-    const size_t row_lds = rows_fwd_hdr_offset<T>(max_ny, mmy) +
-                           sizeof(BlockHeader) * (size_t)std::max(max_pass_blocks, 1);
-    const size_t col_lds = 5 * sizeof(cx<T>) * (size_t)mmx;
-    const size_t inv_lds = 3 * sizeof(cx<T>) * (size_t)mmy;
-    if (max_ny <= 128 && mmy / 2 <= 128)
-        hipLaunchKernelGGL((k_rows_fwd_batched<T, 128>), dim3(rows), dim3(128), row_lds, s, b);
+    const size_t row_lds = rows_fwd_lds<T>(g.max_ny, g.max_my);
+    constexpr size_t line_lds = sizeof(cx<T>) * kLineThreads * 4;
+    if (g.max_ny <= 128 && g.max_my / 2 <= 128)
+        hipLaunchKernelGGL((k_rows_fwd_batched<T, 128>), dim3(g.rows), dim3(128), row_lds, s, b);
     else
-        hipLaunchKernelGGL((k_rows_fwd_batched<T, 256>), dim3(rows), dim3(256), row_lds, s, b);
+        hipLaunchKernelGGL((k_rows_fwd_batched<T, 256>), dim3(g.rows), dim3(256), row_lds, s, b);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cols_batched<T>, dim3(cols), dim3(kColThreads), col_lds, s, b);
+    if (g.max_mx <= 256)
+        hipLaunchKernelGGL((k_cols_batched<T, 8>), dim3(g.col_blocks), dim3(kLineThreads),
+                           line_lds, s, b);
+    else
+        hipLaunchKernelGGL((k_cols_batched<T, 9>), dim3(g.col_blocks), dim3(kLineThreads),
+                           2 * line_lds, s, b);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rows_inv_batched<T>, dim3(rows), dim3(kInvThreads), inv_lds, s, b);
+    if (g.max_my <= 256)
+        hipLaunchKernelGGL((k_rows_inv_batched<T, 8>), dim3(g.inv_blocks), dim3(kLineThreads),
+                           line_lds, s, b);
+    else
+        hipLaunchKernelGGL((k_rows_inv_batched<T, 9>), dim3(g.inv_blocks), dim3(kLineThreads),
+                           2 * line_lds, s, b);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_solve_batched(hipStream_t s, const BatchLaunch &b, bool mixed, int rows,
-                                int cols, int max_mx, int max_ny, int max_my, int max_pass_blocks)
+// Lanes of an FFT of length 2^log2 (any precision).
+static int fft_lanes(int log2) { return (1 << log2) / (log2 == 9 ? 8 : 4); }
+
+int batch_column_blocks(int log2_mx, int hy)
 {
-    return mixed ? launch_solve_batched_t<float>(s, b, rows, cols, max_mx, max_ny, max_my,
-                                                 max_pass_blocks)
-                 : launch_solve_batched_t<double>(s, b, rows, cols, max_mx, max_ny, max_my,
-                                                  max_pass_blocks);
+    const int columns = kLineThreads / (2 * fft_lanes(log2_mx));
+    return (hy + columns) / columns;
+}
+
+int batch_inverse_blocks(int log2_my, int nx)
+{
+    const int rows = kLineThreads / fft_lanes(log2_my);
+    return (nx + rows - 1) / rows;
+}
+
+hipError_t launch_solve_batched(hipStream_t s, const BatchLaunch &b, bool mixed,
+                                const BatchGridShape &g)
+{
+    return mixed ? launch_solve_batched_t<float>(s, b, g) : launch_solve_batched_t<double>(s, b, g);
 }
 
 hipError_t launch_reduce(hipStream_t s, const DepositTarget &dep, int blocks_used, int nx, int ny,

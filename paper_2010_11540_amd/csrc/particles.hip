@@ -891,7 +891,9 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
             h.j0 = j0;
             h.j1 = j1;
             h.count = s_count;
-            h.pad[0] = h.pad[1] = h.pad[2] = 0;
+            h.pad = 0;
+            h.rows = i0 <= i1 ? (uint32_t)i0 | (uint32_t)i1 << 16 : 0xffffu;
+            h.cols = i0 <= i1 ? (uint32_t)j0 | (uint32_t)j1 << 16 : 0xffffu;
             dep.header[bid] = h;
         }
     }

@@ -699,8 +699,7 @@ scpic_status create_impl(scpic_ctx *c, const scpic_grid *grid, int32_t precision
     ALLOC(c->sw.sx, fe * mx);
     ALLOC(c->sw.sy, fe * (hy + 1));
     ALLOC(c->sw.spec_a, ce * (size_t)(hy + 1) * nx);
-    ALLOC(c->sw.spec_bx, ce * (size_t)(hy + 1) * nx);
-    ALLOC(c->sw.spec_by, ce * (size_t)(hy + 1) * nx);
+    ALLOC(c->sw.spec_b, 2 * ce * (size_t)(hy + 1) * nx);
     ALLOC(c->ef, 2 * fe * ncell);
     ALLOC(c->diag_part, sizeof(double) * kMomentBlocks * kMoments);
     ALLOC(c->diag_sums, sizeof(double) * 2 * kMoments);
@@ -1121,8 +1120,8 @@ struct scpic_batch {
     std::vector<scpic_grid> grids;
     std::vector<BatchInstance> inst;  // host copy of the device table
     BatchLaunch launch{};
-    int total_pass_blocks = 0, total_rows = 0, total_cols = 0, max_mx = 0, max_ny = 0, max_my = 0;
-    int max_beam_blocks = 0;  // most pass workgroups of one beam in the current layout
+    int total_pass_blocks = 0;
+    BatchGridShape shape{};
     std::vector<void *> allocations;
     std::vector<BatchSchedule> schedules;
     uint64_t use_counter = 0;
@@ -1233,13 +1232,11 @@ scpic_status batch_layout(scpic_batch *b, int threads, int blocks_per_cu)
     });
     std::vector<uint16_t> pass_inst;
     b->total_pass_blocks = 0;
-    b->max_beam_blocks = 0;
     for (int k : order) {
         BatchInstance &I = b->inst[k];
         I.pass_blocks = blocks[k];
         I.pass_block0 = b->total_pass_blocks;
         b->total_pass_blocks += I.pass_blocks;
-        b->max_beam_blocks = std::max(b->max_beam_blocks, I.pass_blocks);
         for (int t = 0; t < I.pass_blocks; ++t) pass_inst.push_back((uint16_t)k);
         SCPIC_HIP_TRY(hipMemsetAsync(I.dep.header, 0xff, sizeof(BlockHeader) * I.dep.max_blocks, b->stream), "hipMemsetAsync");
     }
@@ -1272,7 +1269,7 @@ scpic_status batch_create_impl(scpic_batch *b, const scpic_grid *grids, const in
     const size_t fe = b->mixed ? sizeof(float) : sizeof(double), ce = 2 * fe;
     const int64_t total = offsets[n_inst];
     std::vector<GridTables> tables;
-    std::vector<uint16_t> row_inst, col_inst;
+    std::vector<uint16_t> row_inst, col_inst, inv_inst;
     size_t pass_table_len = 0;
     b->inst.resize(n_inst);
     b->max_slices.resize(n_inst);
@@ -1295,9 +1292,9 @@ scpic_status batch_create_impl(scpic_batch *b, const scpic_grid *grids, const in
         b->max_slices[k] = std::max(
             1, batch_pass_blocks(n_k, total, (int64_t)b->n_cu * kMaxTuneBlocksPerCu, kMinTuneThreads));
         pass_table_len += (size_t)b->max_slices[k];
-        b->max_mx = std::max(b->max_mx, fft_len(nx));
-        b->max_ny = std::max(b->max_ny, ny);
-        b->max_my = std::max(b->max_my, fft_len(ny));
+        b->shape.max_ny = std::max(b->shape.max_ny, ny);
+        b->shape.max_my = std::max(b->shape.max_my, fft_len(ny));
+        b->shape.max_mx = std::max(b->shape.max_mx, fft_len(nx));
         I.g.nx = nx;
         I.g.ny = ny;
         I.g.x_min = gr.x_min;
@@ -1340,8 +1337,7 @@ scpic_status batch_create_impl(scpic_batch *b, const scpic_grid *grids, const in
         I.sx = gt->sx;
         I.sy = gt->sy;
         BALLOC(I.spec_a, ce * (size_t)(I.my / 2 + 1) * nx);
-        BALLOC(I.spec_bx, ce * (size_t)(I.my / 2 + 1) * nx);
-        BALLOC(I.spec_by, ce * (size_t)(I.my / 2 + 1) * nx);
+        BALLOC(I.spec_b, 2 * ce * (size_t)(I.my / 2 + 1) * nx);
         BALLOC(I.ef, 2 * fe * ncell);
         SCPIC_HIP_TRY(hipMemset(I.dep.carry, 0, sizeof(unsigned long long) * ncell), "hipMemset");
         SCPIC_HIP_TRY(hipMemset(I.dep.header, 0xff, sizeof(BlockHeader) * slices), "hipMemset");
@@ -1359,26 +1355,34 @@ scpic_status batch_create_impl(scpic_batch *b, const scpic_grid *grids, const in
     });
     for (int k : order) {
         BatchInstance &I = b->inst[k];
-        I.row_block0 = b->total_rows;
-        b->total_rows += I.nx;
-        I.col_block0 = b->total_cols;
-        b->total_cols += I.my / 2 + 1;
-        for (int t = 0; t < I.nx; ++t) row_inst.push_back((uint16_t)k);
-        for (int t = 0; t <= I.my / 2; ++t) col_inst.push_back((uint16_t)k);
+        const int cols = batch_column_blocks(I.log2_mx, I.my / 2);
+        const int invs = batch_inverse_blocks(I.log2_my, I.nx);
+        I.row_block0 = b->shape.rows;
+        b->shape.rows += I.nx;
+        I.col_block0 = b->shape.col_blocks;
+        b->shape.col_blocks += cols;
+        I.inv_block0 = b->shape.inv_blocks;
+        b->shape.inv_blocks += invs;
+        row_inst.insert(row_inst.end(), I.nx, (uint16_t)k);
+        col_inst.insert(col_inst.end(), cols, (uint16_t)k);
+        inv_inst.insert(inv_inst.end(), invs, (uint16_t)k);
     }
     BatchInstance *inst_dev;
-    uint16_t *pass_dev, *row_dev, *col_dev;
+    uint16_t *pass_dev, *row_dev, *col_dev, *inv_dev;
     BALLOC(inst_dev, sizeof(BatchInstance) * n_inst);
     BALLOC(pass_dev, sizeof(uint16_t) * pass_table_len);
     BALLOC(row_dev, sizeof(uint16_t) * row_inst.size());
     BALLOC(col_dev, sizeof(uint16_t) * col_inst.size());
+    BALLOC(inv_dev, sizeof(uint16_t) * inv_inst.size());
 #undef BALLOC
     SCPIC_HIP_TRY(hipMemcpy(row_dev, row_inst.data(), sizeof(uint16_t) * row_inst.size(), hipMemcpyHostToDevice), "upload tables");
     SCPIC_HIP_TRY(hipMemcpy(col_dev, col_inst.data(), sizeof(uint16_t) * col_inst.size(), hipMemcpyHostToDevice), "upload tables");
+    SCPIC_HIP_TRY(hipMemcpy(inv_dev, inv_inst.data(), sizeof(uint16_t) * inv_inst.size(), hipMemcpyHostToDevice), "upload tables");
     b->launch.inst = inst_dev;
     b->launch.pass_inst = pass_dev;
     b->launch.row_inst = row_dev;
     b->launch.col_inst = col_dev;
+    b->launch.inv_inst = inv_dev;
     b->launch.n_inst = n_inst;
     b->pass_table = pass_dev;
     SCPIC_HIP_TRY(hipDeviceSynchronize(), "hipDeviceSynchronize");
@@ -1470,8 +1474,7 @@ scpic_status batch_enqueue(scpic_batch *b, hipStream_t s, const scpic_particles 
                                            b->total_pass_blocks, b->pass_threads);
         if (e != hipSuccess) return fail_hip(e, "batched pass launch");
         if (op.deposit) {
-            e = launch_solve_batched(s, b->launch, b->mixed, b->total_rows, b->total_cols,
-                                     b->max_mx, b->max_ny, b->max_my, b->max_beam_blocks);
+            e = launch_solve_batched(s, b->launch, b->mixed, b->shape);
             if (e != hipSuccess) return fail_hip(e, "batched solve launch");
         }
     }
@@ -1802,7 +1805,8 @@ __global__ void __launch_bounds__(256)
         BlockHeader h;
         h.i0 = h.i1 = h.j0 = h.j1 = -1;
         h.count = -1;
-        h.pad[0] = h.pad[1] = h.pad[2] = -1;
+        h.pad = -1;
+        h.rows = h.cols = 0xffffu;
         header[t] = h;
     }
     if (t < ncell) carry[t] = 0ull;

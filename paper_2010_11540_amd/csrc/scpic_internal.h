@@ -37,10 +37,14 @@ constexpr int kMaxPassBlocks = 512;
 
 // Per-block header written by a depositing pass: bounding box of the cells it
 // touched (inclusive; empty when i0 > i1) and how many particles it deposited.
+// rows and cols hold the same box as the row reduction reads it, i0 | i1 << 16
+// and j0 | j1 << 16 (grid sides are at most 256; empty: 0xffff, which no row
+// reaches), half the bytes and registers of the four words.
 struct BlockHeader {
     int32_t i0, i1, j0, j1;
     int32_t count;
-    int32_t pad[3];
+    int32_t pad;
+    uint32_t rows, cols;
 };
 
 // Grid geometry as the kernels see it.  inv_dx / inv_dy are 1.0/dx and
@@ -143,13 +147,14 @@ constexpr int kMaxLineNodes = 512;
 struct BatchInstance {
     int64_t p0, n;                     // particles [p0, p0 + n)
     int32_t pass_block0, pass_blocks;  // its workgroups in a batched pass
-    int32_t row_block0, col_block0;    // its first workgroup in the row / column kernels
+    int32_t row_block0, col_block0, inv_block0;  // its first workgroup in the row-forward,
+                                                 // column and row-inverse kernels
     GridGeom g;
     DepositTarget dep;                 // max_blocks == pass_blocks
     int32_t nx, ny, mx, my, log2_mx, log2_my;
     double scale;                      // 1 / (2^24 N0): charge units -> rho
     const void *stw_x, *stw_y, *ghat_t, *sx, *sy;  // twiddle tables as in SolveWorkspace
-    void *spec_a, *spec_bx, *spec_by;
+    void *spec_a, *spec_b;
     void *ef;                          // interleaved node field
 };
 
@@ -165,10 +170,23 @@ struct BatchStep {
 struct BatchLaunch {
     const BatchInstance *inst;
     const uint16_t *pass_inst;  // [total pass workgroups]
-    const uint16_t *row_inst;   // [sum nx]: row-forward and row-inverse kernels
-    const uint16_t *col_inst;   // [sum (my/2 + 1)]: column kernel
+    const uint16_t *row_inst;   // [sum nx]: row-forward kernel, one row each
+    const uint16_t *col_inst;   // column kernel (batch_column_blocks of each beam)
+    const uint16_t *inv_inst;   // row-inverse kernel (batch_inverse_blocks of each beam)
     int32_t n_inst;
 };
+
+// The grid-phase launches of a batch: their workgroups and bounds of the
+// beams' sizes.
+struct BatchGridShape {
+    int rows = 0, col_blocks = 0, inv_blocks = 0;
+    int max_mx = 0, max_ny = 0, max_my = 0;
+};
+
+// Workgroups of one beam in the batched column kernel (hy + 1 columns of
+// length 2^log2_mx) and row-inverse kernel (nx rows of length 2^log2_my).
+int batch_column_blocks(int log2_mx, int hy);
+int batch_inverse_blocks(int log2_my, int nx);
 
 // ---- launchers (particles.hip) ------------------------------------------
 // ef: interleaved node field (Ex, Ey per node), double or float per mixed.
@@ -223,7 +241,7 @@ struct SolveWorkspace {
     void *ghat_t;        // [my/2+1][mx] real Green's spectrum / (mx my), transposed
     void *sx, *sy;       // [mx] sin(2 pi k / mx)/dx, [my/2+1] sin(2 pi l / my)/dy
     void *spec_a;        // [my/2+1][nx] complex, rows transformed
-    void *spec_bx, *spec_by;  // [nx][my/2+1] complex, after the column pass
+    void *spec_b;        // [nx][my/2+1] pairs of complex (Bx, By), after the column pass
     // node potential (want_phi; for the line density or the B-spline gather):
     // the potential's column-inverse spectrum [nx+2][my/2+1] complex (rows
     // -1..nx) and the potential on nodes -1..nx by -1..ny [(nx+2)*(ny+2)];
@@ -245,11 +263,9 @@ hipError_t launch_solve_partials(hipStream_t s, const SolveWorkspace &w, const D
                                  int blocks_used, double scale, void *ef);
 
 // Field of every beam of a batch from the partials of its last batched pass,
-// interleaved into each beam's ef: rows = sum of nx, cols = sum of (my/2 + 1);
-// max_mx, max_ny, max_my bound every beam's (padded) lengths and
-// max_pass_blocks every beam's pass workgroups.
-hipError_t launch_solve_batched(hipStream_t s, const BatchLaunch &b, bool mixed, int rows,
-                                int cols, int max_mx, int max_ny, int max_my, int max_pass_blocks);
+// interleaved into each beam's ef.
+hipError_t launch_solve_batched(hipStream_t s, const BatchLaunch &b, bool mixed,
+                                const BatchGridShape &g);
 
 // Green's spectrum helper on the host (api.hip): fills ghat_t (FP64,
 // [my/2+1][mx]) for the mx x my periodic kernel (mx >= 2 nx, my >= 2 ny).

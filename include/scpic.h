@@ -258,7 +258,8 @@ scpic_status scpic_diagnose(scpic_ctx *ctx, const scpic_particles *parts, scpic_
  *   SCPIC_OPT_PASS_BLOCKS    workgroups of the particle pass (0 = automatic:
  *                            one per compute unit).
  *   SCPIC_OPT_PASS_THREADS   threads per workgroup of the particle pass
- *                            (256, 512 or 1024; default 1024).
+ *                            (256, 512 or 1024; by default chosen from the
+ *                            particle count).
  *   SCPIC_OPT_SOLVER         SCPIC_SOLVER_OPEN (default): the open-boundary
  *                            convolution of scpic_solve's comment;
  *                            SCPIC_SOLVER_PIPE (nx and ny powers of two, else

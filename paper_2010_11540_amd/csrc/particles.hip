@@ -11,6 +11,7 @@
 // bit-identical counterpart, use explicit fused multiply-adds.
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 #include <vector>
 
 #include "scpic_internal.h"
@@ -22,33 +23,49 @@ namespace {
 
 constexpr int kWave = 64;
 
-// Cell (i, j) holding the particle and its four fixed-point weights for the
-// nodes (i,j), (i+1,j), (i,j+1), (i+1,j+1): the bilinear fractions of
-// Sec. IV-A rounded to 12 bits per axis, summing to exactly 2^24.  False when
-// the particle is outside [0, nx-1) x [0, ny-1) in node units (or NaN).
+// Cell (i, j) holding the particle and its bilinear fractions of Sec. IV-A
+// rounded to 12 bits per axis, a and b of 4096; the fixed-point weights of the
+// nodes (i,j), (i+1,j), (i,j+1), (i+1,j+1) are (4096-a)(4096-b), a(4096-b),
+// (4096-a)b and ab, summing to exactly 2^24.
 struct Cic {
-    int i, j;
-    uint32_t w00, w10, w01, w11;
+    int i, j, a, b;
 };
 
-__device__ __forceinline__ bool cic(const GridGeom &g, double x, double y, Cic &c)
+// Keeps a uniform value in vector registers.  A pass has more uniform values
+// alive in its particle loop than scalar registers (the compiler then parks
+// them in lanes of a vector register and reads each back by an instruction of
+// its own), and vector registers to spare: one workgroup of 1024 threads has a
+// compute unit to itself, 128 registers per lane.  Not where a pass needs the
+// vector registers itself (PIN false: six dimensions, the B-spline field).
+template <bool PIN>
+__device__ __forceinline__ double in_vector(double v)
+{
+    if constexpr (PIN) asm("" : "+v"(v));
+    return v;
+}
+
+// The grid's geometry as cic() uses it.
+struct GridCells {
+    double x_min, y_min, inv_dx, inv_dy, nx1, ny1;
+    template <bool PIN>
+    static __device__ __forceinline__ GridCells of(const GridGeom &g)
+    {
+        return {in_vector<PIN>(g.x_min),  in_vector<PIN>(g.y_min),
+                in_vector<PIN>(g.inv_dx), in_vector<PIN>(g.inv_dy),
+                in_vector<PIN>((double)(g.nx - 1)), in_vector<PIN>((double)(g.ny - 1))};
+    }
+};
+
+// False when the particle is outside [0, nx-1) x [0, ny-1) in node units (or
+// NaN); c is then undefined.
+__device__ __forceinline__ bool cic(const GridCells &g, double x, double y, Cic &c)
 {
     const double tx = (x - g.x_min) * g.inv_dx;
     const double ty = (y - g.y_min) * g.inv_dy;
-    const bool in = tx >= 0.0 && tx < (double)(g.nx - 1) && ty >= 0.0 && ty < (double)(g.ny - 1);
-    // outside (or NaN): evaluate on node 0 so the arithmetic below stays defined
-    const double sx = in ? tx : 0.0, sy = in ? ty : 0.0;
-    const double fi = floor(sx), fj = floor(sy);
-    const uint32_t a = (uint32_t)(int)floor((sx - fi) * 4096.0 + 0.5);
-    const uint32_t b = (uint32_t)(int)floor((sy - fj) * 4096.0 + 0.5);
-    c.i = (int)fi;
-    c.j = (int)fj;
-    const uint32_t a0 = kFracOne - a, b0 = kFracOne - b;
-    c.w00 = a0 * b0;
-    c.w10 = a * b0;
-    c.w01 = a0 * b;
-    c.w11 = a * b;
-    return in;
+    if (!((tx >= 0.0) & (tx < g.nx1) & (ty >= 0.0) & (ty < g.ny1))) return false;
+    cell_fraction(tx, c.i, c.a);
+    cell_fraction(ty, c.j, c.b);
+    return true;
 }
 
 template <typename TE>
@@ -62,26 +79,49 @@ struct Vec2<float> {
     using type = float2;
 };
 
-// Interpolated field at the particle from four (Ex, Ey) nodes: weights / 2^24
-// applied in node order (i,j), (i+1,j), (i,j+1), (i+1,j+1).  row is the
-// distance between rows i and i+1 in the node array.
-template <typename V, typename TE>
-__device__ __forceinline__ void gather_nodes(const V *e, int l00, int row, const Cic &c, TE &fx,
-                                             TE &fy)
-{
-    const V e00 = e[l00], e10 = e[l00 + row], e01 = e[l00 + 1], e11 = e[l00 + row + 1];
-    const TE w00 = (TE)c.w00, w10 = (TE)c.w10, w01 = (TE)c.w01, w11 = (TE)c.w11;
-    fx = (w00 * e00.x + w10 * e10.x + w01 * e01.x + w11 * e11.x) * (TE)(1.0 / kChargeOne);
-    fy = (w00 * e00.y + w10 * e10.y + w01 * e01.y + w11 * e11.y) * (TE)(1.0 / kChargeOne);
-}
+// The four weights as TE, in units of 2^-24 (products of integers up to 2^12:
+// exact).
+template <typename TE>
+struct Weights {
+    TE w00, w10, w01, w11;
+    __device__ __forceinline__ explicit Weights(const Cic &c)
+    {
+        const TE a = (TE)c.a, b = (TE)c.b;
+        const TE a0 = (TE)kFracOne - a, b0 = (TE)kFracOne - b;
+        w00 = a0 * b0;
+        w10 = a * b0;
+        w01 = a0 * b;
+        w11 = a * b;
+    }
+    // of a value at the four nodes, in node order
+    __device__ __forceinline__ TE sum(TE u00, TE u10, TE u01, TE u11) const
+    {
+        return w00 * u00 + w10 * u10 + w01 * u01 + w11 * u11;
+    }
+};
 
-// Potential at the particle from its four nodes, as gather_nodes.
+// The (Ex, Ey) of a cell's four nodes: node (i, j) at byte off of e, row the
+// bytes from row i to i+1.
+template <typename V>
+struct CellField {
+    V e00, e10, e01, e11;
+    __device__ __forceinline__ void load(const V *e, uint32_t off, uint32_t row)
+    {
+        const char *p = reinterpret_cast<const char *>(e);
+        const V *r0 = reinterpret_cast<const V *>(p + off);
+        const V *r1 = reinterpret_cast<const V *>(p + (off + row));
+        e00 = r0[0];
+        e01 = r0[1];
+        e10 = r1[0];
+        e11 = r1[1];
+    }
+};
+
+// Potential at the particle times 2^24 from its four nodes, as gather_nodes.
 template <typename TE>
 __device__ __forceinline__ TE gather_scalar(const TE *u, int l00, int row, const Cic &c)
 {
-    const TE w00 = (TE)c.w00, w10 = (TE)c.w10, w01 = (TE)c.w01, w11 = (TE)c.w11;
-    return (w00 * u[l00] + w10 * u[l00 + row] + w01 * u[l00 + 1] + w11 * u[l00 + row + 1]) *
-           (TE)(1.0 / kChargeOne);
+    return Weights<TE>(c).sum(u[l00], u[l00 + row], u[l00 + 1], u[l00 + row + 1]);
 }
 
 // Field at (x, y) in cell c (c.i, c.j from cic()) from the bicubic B-spline
@@ -131,23 +171,17 @@ __device__ __forceinline__ void bspline_field(const GridGeom &g, const TE *__res
 // Node k of the line and the particle's two fixed-point line weights
 // (4096 - a at k, a at k + 1): t = (sigma - z_min)(1/dz), k = floor(t),
 // a = floor((t - k) 4096 + 0.5), the one-dimensional form of cic().  False
-// outside [0, nz - 1) in node units (or NaN).
+// outside [0, nz - 1) in node units (or NaN); c is then undefined.
 struct LineCic {
-    int k;
-    uint32_t w0, w1;
+    int k, a;
 };
 
 __device__ __forceinline__ bool line_cic(const LineSpec &L, double sg, LineCic &c)
 {
     const double t = (sg - L.z_min) * L.inv_dz;
-    const bool in = t >= 0.0 && t < (double)(L.nz - 1);
-    const double st = in ? t : 0.0;
-    const double fk = floor(st);
-    const uint32_t a = (uint32_t)(int)floor((st - fk) * 4096.0 + 0.5);
-    c.k = (int)fk;
-    c.w0 = kFracOne - a;
-    c.w1 = a;
-    return in;
+    if (!((t >= 0.0) & (t < (double)(L.nz - 1)))) return false;
+    cell_fraction(t, c.k, c.a);
+    return true;
 }
 
 // One element applied to one particle (Sec. III): v <- M v for the linear
@@ -380,19 +414,28 @@ __device__ __forceinline__ int wave_reduce(int v, int identity, Op op)
     v = op(v, __builtin_amdgcn_update_dpp(identity, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
     return __builtin_amdgcn_readlane(v, kWave - 1);
 }
-__device__ __forceinline__ int wave_min(int v)
-{
-    return wave_reduce(v, INT_MAX, [](int a, int b) { return min(a, b); });
-}
-__device__ __forceinline__ int wave_max(int v)
-{
-    return wave_reduce(v, INT_MIN, [](int a, int b) { return max(a, b); });
-}
-__device__ __forceinline__ int wave_sum(int v)
-{
-    return wave_reduce(v, 0, [](int a, int b) { return a + b; });
-}
 
+// Two 16-bit values in one register: cell indices (i in the low half, j in
+// the high one) whose minima and maxima take one instruction for both.
+using Pair = unsigned short __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pair_min(uint32_t u, uint32_t v)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(Pair, u),
+                                                                  __builtin_bit_cast(Pair, v)));
+}
+__device__ __forceinline__ uint32_t pair_max(uint32_t u, uint32_t v)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(Pair, u),
+                                                                  __builtin_bit_cast(Pair, v)));
+}
+__device__ __forceinline__ uint32_t wave_pair_min(uint32_t v)
+{
+    return (uint32_t)wave_reduce((int)v, -1, [](int a, int b) { return (int)pair_min(a, b); });
+}
+__device__ __forceinline__ uint32_t wave_pair_max(uint32_t v)
+{
+    return (uint32_t)wave_reduce((int)v, 0, [](int a, int b) { return (int)pair_max(a, b); });
+}
 // t / w for 0 <= t < 2^16 and 1 <= w <= 2^16: the float product with the
 // rounded reciprocal is within 0.01 of the quotient, so one integer step
 // either way makes it exact.
@@ -408,10 +451,10 @@ __device__ __forceinline__ int div_small(int t, int w, float inv_w)
 // j0..j0+w-1, row-major with row length w.
 struct Box {
     int i0, j0, h, w;
-    // the four nodes of cell (i, j) lie inside
+    // the four nodes of cell (i, j) lie inside (h and w are at least 1)
     __device__ __forceinline__ bool holds_cell(int i, int j) const
     {
-        return i >= i0 && i + 1 < i0 + h && j >= j0 && j + 1 < j0 + w;
+        return ((uint32_t)(i - i0) < (uint32_t)(h - 1)) & ((uint32_t)(j - j0) < (uint32_t)(w - 1));
     }
     __device__ __forceinline__ int at(int i, int j) const { return (i - i0) * w + (j - j0); }
 };
@@ -479,11 +522,102 @@ __device__ __forceinline__ Box charge_tile(const GridGeom &g, const BlockHeader 
     return t;
 }
 
-// The fused particle pass.  Thread t of the launch (T threads in all) walks
-// the particles p = t, t+T, t+2T, ...: consecutive lanes take consecutive
-// particles, so every SoA load and store is coalesced, and the next
-// particle's loads (the next two in the streamed form) are issued before the
-// current one is worked on.  For each particle:
+// What the lanes of a pass hold of one particle between its load and its use.
+struct Loaded {
+    double x, px, y, py, sg, psg;
+    float w;
+    uint8_t lost;
+};
+
+// Waits for the loads issued so far (not for LDS).  A block that few waves
+// enter and that loads registers waits inside, so that the code after it, which
+// every wave runs, need not wait for memory on its account.
+__device__ __forceinline__ void wait_loads()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt 0, expcnt and lgkmcnt any
+}
+
+// The particle, counted from p0, of this lane in a wave's round of 64 from p0
+// on (p0 < n): its own, or the last one for a lane past it.
+__device__ __forceinline__ uint32_t round_lane(int64_t left)
+{
+    const uint32_t last = left < kWave ? (uint32_t)left - 1u : kWave - 1u;
+    return min((uint32_t)threadIdx.x & (kWave - 1u), last);
+}
+
+// The particles of a wave's round of 64 from p0 on, `left` of them: the addresses are the
+// arrays' uniform pointers at p0 (scalar registers) plus the lane's byte
+// offset.  Every lane loads (round_lane), and the flags and weights are not
+// looked at here, which would wait for the loads.  Without a
+// lost array the flag loads some byte that the caller ignores, so that the
+// number of loads in flight does not depend on a branch.
+template <bool SIX, bool NT>
+__device__ __forceinline__ Loaded load_particles(const ParticlePtrs &P, int64_t p0, int64_t left,
+                                                 bool weights)
+{
+    const uint32_t lane = round_lane(left);
+    const uint8_t *lost = P.lost ? P.lost + p0 : reinterpret_cast<const uint8_t *>(P.x + p0);
+    Loaded v;
+    v.w = 1.0f;
+    if (weights) v.w = (P.w + p0)[lane];
+    if constexpr (NT) {
+        v.x = __builtin_nontemporal_load(P.x + p0 + lane);
+        v.px = __builtin_nontemporal_load(P.px + p0 + lane);
+        v.y = __builtin_nontemporal_load(P.y + p0 + lane);
+        v.py = __builtin_nontemporal_load(P.py + p0 + lane);
+    } else {
+        v.x = (P.x + p0)[lane];
+        v.px = (P.px + p0)[lane];
+        v.y = (P.y + p0)[lane];
+        v.py = (P.py + p0)[lane];
+    }
+    if constexpr (SIX) {
+        v.sg = (P.sigma + p0)[lane];
+        v.psg = (P.psigma + p0)[lane];
+    }
+    v.lost = lost[lane];
+    return v;
+}
+
+// Adds a particle's four weights to the workgroup's tile, where l is the tile
+// cell of node (i, j) and row the tile's row length.  A 32-bit cell wraps
+// after 2^32 units (256 particles on one node); the atomic's old value shows
+// the wrap and the lost 2^32 goes to the carry grid (cg: node (i, j) there).
+// All four atomics issue before any check.  (Atomics without a returned value,
+// the tile's sum against 2^24 per particle at the end and a second deposit
+// where it fell short were no faster: 30.1 and 29.7 us per step at 1e6
+// particles.)
+__device__ __forceinline__ void deposit_cell(uint32_t *lq, int l, int row,
+                                             unsigned long long *carry, int cg, int ny,
+                                             const Cic &c)
+{
+    const uint32_t a = (uint32_t)c.a, b = (uint32_t)c.b;
+    const uint32_t a0 = kFracOne - a, b0 = kFracOne - b;
+    const uint32_t w00 = __umul24(a0, b0), w10 = __umul24(a, b0), w01 = __umul24(a0, b),
+                   w11 = __umul24(a, b);
+    const uint32_t o00 = atomicAdd(&lq[l], w00);
+    const uint32_t o10 = atomicAdd(&lq[l + row], w10);
+    const uint32_t o01 = atomicAdd(&lq[l + 1], w01);
+    const uint32_t o11 = atomicAdd(&lq[l + row + 1], w11);
+    if (o00 + w00 < o00) atomicAdd(&carry[cg], 1ull << 32);
+    if (o10 + w10 < o10) atomicAdd(&carry[cg + ny], 1ull << 32);
+    if (o01 + w01 < o01) atomicAdd(&carry[cg + 1], 1ull << 32);
+    if (o11 + w11 < o11) atomicAdd(&carry[cg + ny + 1], 1ull << 32);
+}
+
+// The fused particle pass.  Wave w of workgroup bid of the nblk of a launch
+// walks its rounds of 64 particles from bid * blockDim.x + 64 w on in steps of
+// T = nblk * blockDim.x: consecutive lanes take consecutive particles, so
+// every SoA load and store is coalesced.  The loads of the next round (of the
+// one after next in the streamed form) are issued in each round: before the
+// gathers from LDS, after those from the L2 (memory operations complete in
+// order, and these would otherwise wait for memory instead of the cache).  For the
+// compiler to count on that order no common load or store stands behind a
+// branch: a spare lane of a wave's last round repeats the last particle, which
+// is another lane's of the same wave (the same instructions load and store it
+// for both), but for its deposit, and a frozen particle stores its old
+// coordinates.
+// For each particle:
 //   KICK     gather the node field at the particle with the deposit weights
 //            and kick px, py by kappa * w_p * E (w_p = 1 without weights);
 //            a particle found outside the domain is marked lost and frozen;
@@ -491,14 +625,30 @@ __device__ __forceinline__ Box charge_tile(const GridGeom &g, const BlockHeader 
 //   DEPOSIT  add the particle's four weights to the workgroup's LDS tile of
 //            the charge grid (nodes outside the tile: global atomics on the
 //            carry grid); particles outside the domain are marked lost.
-// When the whole charge grid fits in LDS and the workgroup's threads have few
-// particles each, the whole grid is the tile and gathers read the L2-resident
-// field.  Otherwise the tile covers the box the workgroup's
+// With WHOLE (whole_tile, the host's rule) the whole grid is the tile and
+// gathers read the L2-resident field: the set-up then needs nothing of the
+// previous pass's box and no field staging, only the zeroing of the tile.
+// Otherwise the tile covers the box the workgroup's
 // previous deposit recorded (its header; a workgroup owns the same particles
 // at every step of a track), and that box of the field, which holds every
 // node the kick gathers from, is staged in LDS beside the tile when it fits.
 // At the end each workgroup writes the bounding box of its tile cells to its
 // slice of the partials (no global atomics).
+//
+// What bounds it: the L2 traffic of the gathers (with every lane gathering
+// from one line, 1e6 particles on 128^2 took 28.3 us per step instead of 31.7:
+// hence the box staged in LDS), about 8 us of set-up, flush and launch, and
+// from there the last-level cache (a round of 2.6e5 particles adds 2.3 us, 7.3
+// TB/s).  The order of its memory operations, the resident map, the cells by
+// one conversion and the box moved by direct loads together: 18.0 -> 15.5 us
+// at 1e6 particles (FP64), the 64-beam scan 222 -> 195 us per step.
+//
+// FIRST: the kind of the pass's first element when the caller knows it to be a
+// linear map (0: any elements).  The map's matrix then stays in registers for
+// the whole pass; read element by element inside the particle loop, its kind
+// and its parameters were two dependent scalar loads per element and round,
+// which nothing hid.
+//
 // MODE is a set of flags (0: four-dimensional).  1: the particles carry sigma
 // and p_sigma and els may hold thick elements; sigma is loaded and stored with
 // the transverse coordinates.  2: six-dimensional, with the long-bunch line
@@ -514,11 +664,11 @@ __device__ __forceinline__ Box charge_tile(const GridGeom &g, const BlockHeader 
 // nodes -1..nx by -1..ny.
 // 8: the four transverse coordinates are streamed with non-temporal loads and
 // stores (particle arrays far larger than the last-level cache, which they
-// would only churn; smaller ones stay cached between passes).
+// would only churn; smaller ones stay cached between passes).  16: WHOLE.
 // The body is shared by the single-beam kernel and the batched one: bid is
 // the workgroup's index among the nblk workgroups working on beam P (its
-// slice of the partials and its header), T = nblk * blockDim.x.
-template <typename TE, bool KICK, bool DEPOSIT, int MODE>
+// slice of the partials and its header).
+template <typename TE, bool KICK, bool DEPOSIT, int MODE, int FIRST>
 __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom &g,
                                           const TE *__restrict__ ef, double kappa,
                                           const PassElements &els, const DepositTarget &dep,
@@ -530,65 +680,69 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     constexpr bool SIX = (MODE & 1) != 0 || LINE;
     constexpr bool BSPL = (MODE & 4) != 0;
     constexpr bool NT = (MODE & 8) != 0;
+    constexpr bool WHOLE = (MODE & 16) != 0;
+    static_assert(!WHOLE || DEPOSIT, "the tile is the depositing passes'");
+    static_assert(!NT || !SIX, "the streamed pass is four-dimensional");
+    static_assert(!FIRST || !SIX, "a resident first element is four-dimensional");
     extern __shared__ __align__(16) unsigned char lds_all[];
-    // LDS: [line histogram (MODE 2)][charge tile][staged field box].  The
-    // histogram counts in 32 bits: a workgroup adds 4096 per particle and the
-    // host launches no workgroup with more than 2^20 particles.
+    // A pass that uses LDS reads its elements' parameters from there (one
+    // broadcast read per value) but for a resident first element: read into
+    // scalar registers, they would displace the loop's other uniform values.
+    constexpr bool EL_LDS = SIX || KICK || DEPOSIT;
+    // LDS: [element parameters (four-dimensional passes)][line histogram
+    // (MODE 2)][charge tile][staged field box].  The histogram counts in 32
+    // bits: a workgroup adds 4096 per particle and the host launches no
+    // workgroup with more than 2^20 particles.
+    const unsigned el_bytes =
+        EL_LDS && !SIX && els.n_el > (FIRST ? 1 : 0) ? (unsigned)els.n_el * 128u : 0u;
     const unsigned line_bytes = LINE ? ((unsigned)line.nz * 4u + 15u) & ~15u : 0u;
     uint32_t *lh = reinterpret_cast<uint32_t *>(lds_all);
-    unsigned char *const lds = lds_all + line_bytes;
-    lds_bytes -= line_bytes;
+    unsigned char *const lds = lds_all + el_bytes + line_bytes;
+    lds_bytes -= el_bytes + line_bytes;
     __shared__ int s_box[4];
     __shared__ int s_count;
-    // Six-dimensional passes read their elements' parameters from LDS (one
-    // broadcast read per value) rather than from scalar registers, which the
-    // thick elements' many parameters would otherwise spill.
-    __shared__ double s_el[SIX ? kMaxPassElements * 16 : 1];
-    static_assert(sizeof(s_el) + 256 <= kPassStaticLds, "static LDS beyond the reserved share");
+    __shared__ double s_el6[SIX ? kMaxPassElements * 16 : 1];
+    static_assert(sizeof(s_el6) + 256 <= kPassStaticLds, "static LDS beyond the reserved share");
+    double *const s_el = SIX ? s_el6 : reinterpret_cast<double *>(lds_all);
+    constexpr bool PIN = !SIX && !BSPL;
+    constexpr bool PIN_GRID = PIN && !NT && FIRST != SCPIC_EL_LIN4X4;
+    constexpr bool PIN_MAP = PIN && !(NT && FIRST == SCPIC_EL_LIN4X4);
+    const GridCells gc = GridCells::of<PIN_GRID>(g);
+    const int n_el = els.n_el;
     const int64_t T = (int64_t)nblk * blockDim.x;
-    int64_t p = (int64_t)bid * blockDim.x + threadIdx.x;
+    int64_t p0 = (int64_t)bid * blockDim.x +
+                 kWave * __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const bool weights = KICK && !LINE && P.w;
 
-    // first particle's loads go out before the LDS set-up
-    double x = 0, px = 0, y = 0, py = 0, sg = 0, psg = 0;
-    float wp = 1.0f;
-    uint8_t lf = 1;
-    if (p < P.n) {
-        x = P.x[p];
-        px = P.px[p];
-        y = P.y[p];
-        py = P.py[p];
-        if constexpr (SIX) {
-            sg = P.sigma[p];
-            psg = P.psigma[p];
-        }
-        lf = P.lost ? P.lost[p] : 0;
-        if (KICK && P.w) wp = P.w[p];
-    }
+    // first round's loads go out before the LDS set-up
+    Loaded cur;
+    if (p0 < P.n) cur = load_particles<SIX, false>(P, p0, P.n - p0, weights);
 
-    // When the whole charge grid fits in LDS and each thread has few
-    // particles, the whole grid is the tile and the kick gathers from the
-    // L2-resident field: the set-up then needs nothing from the previous pass
-    // (no header read, no field staging), only the zeroing of the tile.
-    // Otherwise the previous pass's header sizes the tile and the staged
-    // field box, whose set-up pays off over many particles per thread.
-    constexpr int64_t kWholeMaxPerThread = 4;
-    const bool whole = DEPOSIT && (size_t)g.nx * g.ny <= lds_bytes / sizeof(uint32_t) &&
-                       P.n <= kWholeMaxPerThread * T;
     BlockHeader hd;
     hd.i0 = -1;
     hd.i1 = -2;
     hd.j0 = -1;
     hd.j1 = -2;
-    if ((KICK || DEPOSIT) && !whole) hd = dep.header[bid];
+    if ((KICK || DEPOSIT) && !WHOLE) hd = dep.header[bid];
     // The kick stages the field over the previous box (every node it gathers
-    // from) when that box fits in LDS beside the charge tile.
+    // from) when that box fits in LDS beside the charge tile.  The staging
+    // moves units of 16 bytes, kUnitNodes nodes each: the box's columns are
+    // rounded out to whole units (ny is a multiple of 4), and 64 units of
+    // slack follow the box.
+    constexpr int kUnitNodes = 16 / (int)sizeof(V);
     const bool known = hd.i0 >= 0 && hd.i0 <= hd.i1 && hd.j0 >= 0 && hd.j0 <= hd.j1 &&
                        hd.i1 < g.nx && hd.j1 < g.ny;
-    const Box fbox{hd.i0, hd.j0, hd.i1 - hd.i0 + 1, hd.j1 - hd.j0 + 1};
-    const size_t field_bytes =
-        (KICK && !BSPL && !whole && known) ? ((size_t)fbox.h * fbox.w + 2) * sizeof(V) : 0;
-    // LDS layout: [charge tile][staged field box + 2 nodes of slack]
-    Box tile{0, 0, 0, 0};
+    Box fbox{0, 0, 1, 1};
+    if (known) {
+        const int j0 = hd.j0 & ~(kUnitNodes - 1), j1 = hd.j1 | (kUnitNodes - 1);
+        fbox = Box{hd.i0, j0, hd.i1 - hd.i0 + 1, j1 - j0 + 1};
+    }
+    constexpr size_t kSlack = 64 * 16;
+    const size_t field_bytes = (KICK && !BSPL && !WHOLE && known)
+                                   ? (size_t)fbox.h * fbox.w * sizeof(V) + kSlack
+                                   : 0;
+    // LDS layout: [charge tile][staged field box and slack]
+    Box tile{0, 0, 1, 1};
     size_t tile_bytes = 0;
     if constexpr (DEPOSIT) {
         // the widest margin (12, 8, 4 or 0 cells) that leaves room for the
@@ -601,58 +755,55 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
                 m -= 4;
             if (m >= 0) margin = m;
         }
-        tile = whole ? Box{0, 0, g.nx, g.ny} : charge_tile(g, hd, lds_bytes, margin);
+        tile = WHOLE ? Box{0, 0, g.nx, g.ny} : charge_tile(g, hd, lds_bytes, margin);
         tile_bytes = sizeof(uint32_t) * (size_t)tile.h * tile.w;
     }
     uint32_t *lq = reinterpret_cast<uint32_t *>(lds);
     V *le = reinterpret_cast<V *>(lds + tile_bytes);
-    Box ebox{0, 0, 0, 0};
+    Box ebox{0, 0, 1, 1};
     bool staged = false;
     if constexpr (KICK) {
-        ebox = fbox;
         staged = field_bytes && field_bytes + tile_bytes <= (size_t)lds_bytes;
-        if (field_bytes && !staged && tile_bytes < (size_t)lds_bytes) {
+        if (staged) ebox = fbox;
+        if (field_bytes && !staged && tile_bytes + kSlack < (size_t)lds_bytes) {
             // The whole box does not fit beside the tile: stage its centre,
             // as much as fits, when that keeps at least half of its nodes
             // (the box's edges hold only the tails of the distribution; a
             // particle outside the staged part gathers from L2).
-            const int64_t room = (int64_t)(((size_t)lds_bytes - tile_bytes) / sizeof(V)) - 2;
+            const int64_t room = (int64_t)(((size_t)lds_bytes - tile_bytes - kSlack) / sizeof(V));
             if (2 * room >= (int64_t)fbox.h * fbox.w) {
                 int i0 = fbox.i0, i1 = fbox.i0 + fbox.h - 1, j0 = fbox.j0, j1 = fbox.j0 + fbox.w - 1;
                 while ((int64_t)(i1 - i0 + 1) * (j1 - j0 + 1) > room) {
-                    // trim the longer side, one node at each end
+                    // trim the longer side, one node (one unit) at each end
                     if (i1 - i0 >= j1 - j0) {
                         ++i0;
                         --i1;
                     } else {
-                        ++j0;
-                        --j1;
+                        j0 += kUnitNodes;
+                        j1 -= kUnitNodes;
                     }
                 }
-                ebox = Box{i0, j0, i1 - i0 + 1, j1 - j0 + 1};
-                staged = ebox.h >= 2 && ebox.w >= 2;
+                staged = i1 > i0 && j1 > j0;
+                if (staged) ebox = Box{i0, j0, i1 - i0 + 1, j1 - j0 + 1};
             }
         }
         if (staged) {
-            // four nodes per thread per round; indices past the box repeat
-            // its last node, so every load and store is unconditional and
-            // the four loads are in flight before the first store
+            // A wave moves 64 units at a time straight to consecutive LDS (lane
+            // l to slot l; lanes past the box repeat its last unit into the
+            // slack): every load is in flight at once and none passes through
+            // a register.
             const V *ev = reinterpret_cast<const V *>(ef);
-            const int nodes = ebox.h * ebox.w;
-            const int nt = (int)blockDim.x;
-            const float inv_w = 1.0f / (float)ebox.w;
-            auto node = [&](int t) {
-                const int r = div_small(t, ebox.w, inv_w);
-                return (ebox.i0 + r) * g.ny + ebox.j0 + (t - r * ebox.w);
-            };
-            for (int t0 = threadIdx.x; t0 < nodes; t0 += 4 * nt) {
-                const int ta = t0, tb = min(t0 + nt, nodes - 1), tc = min(t0 + 2 * nt, nodes - 1),
-                          td = min(t0 + 3 * nt, nodes - 1);
-                const V va = ev[node(ta)], vb = ev[node(tb)], vc = ev[node(tc)], vd = ev[node(td)];
-                le[ta] = va;
-                le[tb] = vb;
-                le[tc] = vc;
-                le[td] = vd;
+            const int wu = ebox.w / kUnitNodes, units = ebox.h * wu;
+            const float inv_w = 1.0f / (float)wu;
+            const int lane = (int)threadIdx.x & (kWave - 1);
+            for (int t0 = kWave * __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+                 t0 < units; t0 += (int)blockDim.x) {
+                const int t = min(t0 + lane, units - 1);
+                const int r = div_small(t, wu, inv_w);
+                const V *src = ev + (ebox.i0 + r) * g.ny + ebox.j0 + (t - r * wu) * kUnitNodes;
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void *)(uintptr_t)src,
+                    (__attribute__((address_space(3))) void *)(le + t0 * kUnitNodes), 16, 0, 0);
             }
         }
     }
@@ -670,201 +821,187 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
             s_count = 0;
         }
     }
-    if constexpr (SIX)
-        for (int t = threadIdx.x; t < els.n_el * 16; t += blockDim.x)
+    if (SIX || el_bytes)
+        for (int t = threadIdx.x; t < n_el * 16; t += blockDim.x)
             s_el[t] = els.p[t >> 4][t & 15];
+    // the resident first element
+    double m0[16] = {};
+    if constexpr (FIRST == SCPIC_EL_LIN2X2 || FIRST == SCPIC_EL_LIN4X4)
+#pragma unroll
+        for (int k = 0; k < (FIRST == SCPIC_EL_LIN4X4 ? 16 : 8); ++k)
+            m0[k] = in_vector<PIN_MAP>(els.p[0][k]);
+    wait_loads();  // the first round and the staged field
     if (KICK || DEPOSIT || SIX) __syncthreads();
 
-    const bool moves = KICK || els.n_el > 0;
-    int bi0 = INT_MAX, bi1 = -1, bj0 = INT_MAX, bj1 = -1, cnt = 0;
-    // The streamed form keeps two particles in flight per lane ahead of the
-    // one worked on (its loads come from memory, not the last-level cache):
-    // the second is loaded here and moves up each iteration.
-    static_assert(!NT || !SIX, "the streamed pass is four-dimensional");
-    double xa = 0, pxa = 0, ya = 0, pya = 0;
-    float wa = 1.0f;
-    uint8_t lfa = 1;
-    if constexpr (NT) {
-        const int64_t pa = p + T;
-        if (pa < P.n) {
-            xa = __builtin_nontemporal_load(&P.x[pa]);
-            pxa = __builtin_nontemporal_load(&P.px[pa]);
-            ya = __builtin_nontemporal_load(&P.y[pa]);
-            pya = __builtin_nontemporal_load(&P.py[pa]);
-            lfa = P.lost ? P.lost[pa] : 0;
-            if (KICK && P.w) wa = P.w[pa];
-        }
-    }
-    for (; p < P.n; p += T) {
-        const int64_t pn = p + (NT ? 2 : 1) * T;
-        double xn = 0, pxn = 0, yn = 0, pyn = 0, sgn = 0, psgn = 0;
-        float wn = 1.0f;
-        uint8_t lfn = 1;
-        if (pn < P.n) {
-            if constexpr (NT) {
-                xn = __builtin_nontemporal_load(&P.x[pn]);
-                pxn = __builtin_nontemporal_load(&P.px[pn]);
-                yn = __builtin_nontemporal_load(&P.y[pn]);
-                pyn = __builtin_nontemporal_load(&P.py[pn]);
-            } else {
-                xn = P.x[pn];
-                pxn = P.px[pn];
-                yn = P.y[pn];
-                pyn = P.py[pn];
+    const bool moves = KICK || n_el > 0;
+    // the kick's weights and the charge of a node are in units of 2^-24
+    constexpr double kUnit = 1.0 / kChargeOne;
+    uint32_t lo = 0xffffffffu, hi = 0;  // lowest and highest cell touched, i | j << 16
+    int cnt = 0;                        // particles deposited by the wave
+    // The streamed form keeps two rounds in flight ahead of the one worked on
+    // (its loads come from memory, not the last-level cache).
+    Loaded ahead;
+    if (NT && p0 < P.n)
+        ahead = load_particles<SIX, true>(P, p0 + T < P.n ? p0 + T : p0,
+                                          p0 + T < P.n ? P.n - p0 - T : 1, weights);
+    const bool has_lost = P.lost != nullptr;
+    for (; p0 < P.n; p0 += T) {
+        const uint32_t lane = round_lane(P.n - p0);
+        bool act = (cur.lost == 0) | !has_lost;
+        // the last rounds have nothing to load: every lane loads one particle
+        const bool more = p0 + (NT ? 2 : 1) * T < P.n;
+        const int64_t pn = more ? p0 + (NT ? 2 : 1) * T : p0, left = more ? P.n - pn : 1;
+        Loaded next;
+        if constexpr (!WHOLE) next = load_particles<SIX, NT>(P, pn, left, weights);
+        // the gathers
+        Cic ck;
+        LineCic lck;
+        bool in = false;
+        CellField<V> ev;
+        if constexpr (KICK) {
+            in = act && cic(gc, cur.x, cur.y, ck) && (!LINE || line_cic(line, cur.sg, lck));
+            if constexpr (!BSPL) {
+                const V *ge = reinterpret_cast<const V *>(ef);
+                const uint32_t row = (uint32_t)sizeof(V) * (uint32_t)g.ny;
+                if constexpr (WHOLE) {
+                    if (in) ev.load(ge, (uint32_t)sizeof(V) * (uint32_t)(ck.i * g.ny + ck.j), row);
+                } else {
+                    const bool near = in && staged && ebox.holds_cell(ck.i, ck.j);
+                    if (near)
+                        ev.load(le, (uint32_t)sizeof(V) * (uint32_t)ebox.at(ck.i, ck.j),
+                                (uint32_t)sizeof(V) * (uint32_t)ebox.w);
+                    if (in && !near) {
+                        ev.load(ge, (uint32_t)sizeof(V) * (uint32_t)(ck.i * g.ny + ck.j), row);
+                        wait_loads();
+                    }
+                }
             }
-            if constexpr (SIX) {
-                sgn = P.sigma[pn];
-                psgn = P.psigma[pn];
-            }
-            lfn = P.lost ? P.lost[pn] : 0;
-            if (KICK && P.w) wn = P.w[pn];
         }
-        bool act = lf == 0;
-        if (KICK && act) {
-            Cic c;
-            LineCic lc;
-            const bool in = cic(g, x, y, c) && (!LINE || line_cic(line, sg, lc));
+        if constexpr (WHOLE) next = load_particles<SIX, NT>(P, pn, left, weights);
+        double x = cur.x, px = cur.px, y = cur.y, py = cur.py, sg = cur.sg, psg = cur.psg;
+        if constexpr (KICK) {
             if (in) {
                 TE fx, fy;
-                if constexpr (BSPL)
-                    bspline_field(g, ef, x, y, c, fx, fy);
-                else if (staged && ebox.holds_cell(c.i, c.j))
-                    gather_nodes(le, ebox.at(c.i, c.j), ebox.w, c, fx, fy);
-                else
-                    gather_nodes(reinterpret_cast<const V *>(ef), c.i * g.ny + c.j, g.ny, c, fx, fy);
+                if constexpr (BSPL) {
+                    bspline_field(g, ef, x, y, ck, fx, fy);
+                } else {
+                    const Weights<TE> w(ck);
+                    fx = w.sum(ev.e00.x, ev.e10.x, ev.e01.x, ev.e11.x);
+                    fy = w.sum(ev.e00.y, ev.e10.y, ev.e01.y, ev.e11.y);
+                }
                 if constexpr (LINE) {
-                    const double w0 = (double)lc.w0, w1 = (double)lc.w1;
-                    const double wl = (w0 * line.lw[lc.k] + w1 * line.lw[lc.k + 1]) / 4096.0;
-                    const double dl = (w0 * line.ld[lc.k] + w1 * line.ld[lc.k + 1]) / 4096.0;
+                    const double w1 = (double)lck.a, w0 = 4096.0 - w1;
+                    const double wl = (w0 * line.lw[lck.k] + w1 * line.lw[lck.k + 1]) / 4096.0;
+                    const double dl = (w0 * line.ld[lck.k] + w1 * line.ld[lck.k + 1]) / 4096.0;
                     const TE fp = gather_scalar(reinterpret_cast<const TE *>(line.phi),
-                                                (c.i + 1) * (g.ny + 2) + c.j + 1, g.ny + 2, c);
-                    const double k = kappa * wl;
+                                                (ck.i + 1) * (g.ny + 2) + ck.j + 1, g.ny + 2, ck);
+                    const double k = kappa * wl * kUnit;
                     px = px + k * (double)fx;
                     py = py + k * (double)fy;
-                    psg = psg - line.gamma0 * kappa * (double)fp * dl;
+                    psg = psg - line.gamma0 * kappa * ((double)fp * kUnit) * dl;
                 } else {
-                    const double k = kappa * (double)wp;
+                    // (kappa 2^-24) w E: the power of two may go anywhere
+                    const double k0 = BSPL ? kappa : kappa * kUnit;
+                    const double k = weights ? k0 * (double)cur.w : k0;
                     px = px + k * (double)fx;
                     py = py + k * (double)fy;
                 }
-            } else if (P.lost) {
-                P.lost[p] = 1;
+            } else if (act && has_lost) {
+                (P.lost + p0)[lane] = 1;
                 act = false;
             }
         }
+        bool hit = false;
         if (act) {
             if constexpr (SIX) {
                 const Chroma ck = chroma(psg);
-                for (int e = 0; e < els.n_el; ++e)
+                for (int e = 0; e < n_el; ++e)
                     apply_element6(els.kind[e], s_el + 16 * e, x, px, y, py, sg, ck);
+            } else if constexpr (FIRST != 0) {
+                apply_element(FIRST, m0, x, px, y, py);
+                for (int e = 1; e < n_el; ++e)
+                    apply_element(els.kind[e], s_el + 16 * e, x, px, y, py);
             } else {
-                for (int e = 0; e < els.n_el; ++e)
-                    apply_element(els.kind[e], els.p[e], x, px, y, py);
-            }
-            if (moves) {
-                // the kick changes only the momenta; the elements move the
-                // particle (a kick-only pass writes px and py alone)
-                const bool shifts = els.n_el > 0;
-                if constexpr (NT) {
-                    if (shifts) {
-                        __builtin_nontemporal_store(x, &P.x[p]);
-                        __builtin_nontemporal_store(y, &P.y[p]);
-                    }
-                    __builtin_nontemporal_store(px, &P.px[p]);
-                    __builtin_nontemporal_store(py, &P.py[p]);
-                } else {
-                    if (shifts) {
-                        P.x[p] = x;
-                        P.y[p] = y;
-                    }
-                    P.px[p] = px;
-                    P.py[p] = py;
-                }
-                if constexpr (SIX)
-                    if (shifts) P.sigma[p] = sg;
-                if constexpr (LINE && KICK) P.psigma[p] = psg;
+                for (int e = 0; e < n_el; ++e)
+                    apply_element(els.kind[e], EL_LDS ? s_el + 16 * e : els.p[e], x, px, y, py);
             }
             if constexpr (DEPOSIT) {
                 Cic c;
                 LineCic lc;
-                if (cic(g, x, y, c) && (!LINE || line_cic(line, sg, lc))) {
+                const bool inside = cic(gc, x, y, c) && (!LINE || line_cic(line, sg, lc));
+                hit = inside & ((threadIdx.x & (kWave - 1)) == lane);
+                if (hit) {
                     if constexpr (LINE) {
-                        atomicAdd(&lh[lc.k], lc.w0);
-                        atomicAdd(&lh[lc.k + 1], lc.w1);
+                        atomicAdd(&lh[lc.k], (uint32_t)(kFracOne - lc.a));
+                        atomicAdd(&lh[lc.k + 1], (uint32_t)lc.a);
                     }
-                    if (tile.holds_cell(c.i, c.j)) {
-                        // A 32-bit tile cell wraps after 2^32 units (256
-                        // particles on one node); the atomic's old value
-                        // shows the wrap and the lost 2^32 goes to the carry
-                        // grid.  All four atomics issue before any check.
-                        const int l = tile.at(c.i, c.j);
-                        const int cg = c.i * g.ny + c.j;
-                        const uint32_t o00 = atomicAdd(&lq[l], c.w00);
-                        const uint32_t o10 = atomicAdd(&lq[l + tile.w], c.w10);
-                        const uint32_t o01 = atomicAdd(&lq[l + 1], c.w01);
-                        const uint32_t o11 = atomicAdd(&lq[l + tile.w + 1], c.w11);
-                        if (o00 + c.w00 < o00) atomicAdd(&dep.carry[cg], 1ull << 32);
-                        if (o10 + c.w10 < o10) atomicAdd(&dep.carry[cg + g.ny], 1ull << 32);
-                        if (o01 + c.w01 < o01) atomicAdd(&dep.carry[cg + 1], 1ull << 32);
-                        if (o11 + c.w11 < o11) atomicAdd(&dep.carry[cg + g.ny + 1], 1ull << 32);
-                        bi0 = min(bi0, c.i);
-                        bi1 = max(bi1, c.i + 1);
-                        bj0 = min(bj0, c.j);
-                        bj1 = max(bj1, c.j + 1);
+                    if (WHOLE || tile.holds_cell(c.i, c.j)) {
+                        deposit_cell(lq, tile.at(c.i, c.j), tile.w, dep.carry,
+                                     c.i * g.ny + c.j, g.ny, c);
+                        const uint32_t cell = (uint32_t)c.i | (uint32_t)c.j << 16;
+                        lo = pair_min(lo, cell);
+                        hi = pair_max(hi, cell);
                     } else {
-                        const int cg = c.i * g.ny + c.j;
-                        atomicAdd(&dep.carry[cg], (unsigned long long)c.w00);
-                        atomicAdd(&dep.carry[cg + g.ny], (unsigned long long)c.w10);
-                        atomicAdd(&dep.carry[cg + 1], (unsigned long long)c.w01);
-                        atomicAdd(&dep.carry[cg + g.ny + 1], (unsigned long long)c.w11);
+                        const uint32_t a = (uint32_t)c.a, b = (uint32_t)c.b;
+                        const uint32_t a0 = kFracOne - a, b0 = kFracOne - b;
+                        unsigned long long *cg = dep.carry + (c.i * g.ny + c.j);
+                        atomicAdd(cg, (unsigned long long)(a0 * b0));
+                        atomicAdd(cg + g.ny, (unsigned long long)(a * b0));
+                        atomicAdd(cg + 1, (unsigned long long)(a0 * b));
+                        atomicAdd(cg + g.ny + 1, (unsigned long long)(a * b));
                     }
-                    ++cnt;
-                } else if (P.lost) {
-                    P.lost[p] = 1;
+                } else if (has_lost & !inside) {
+                    (P.lost + p0)[lane] = 1;
                 }
             }
         }
-        if constexpr (NT) {
-            x = xa;
-            px = pxa;
-            y = ya;
-            py = pya;
-            wp = wa;
-            lf = lfa;
-            xa = xn;
-            pxa = pxn;
-            ya = yn;
-            pya = pyn;
-            wa = wn;
-            lfa = lfn;
-        } else {
-            x = xn;
-            px = pxn;
-            y = yn;
-            py = pyn;
-            if constexpr (SIX) {
-                sg = sgn;
-                psg = psgn;
+        if (moves) {
+            // the kick changes only the momenta; the elements move the
+            // particle (a kick-only pass writes px and py alone)
+            const bool shifts = FIRST != 0 || n_el > 0;
+            if constexpr (NT) {
+                if (shifts) {
+                    __builtin_nontemporal_store(x, P.x + p0 + lane);
+                    __builtin_nontemporal_store(y, P.y + p0 + lane);
+                }
+                __builtin_nontemporal_store(px, P.px + p0 + lane);
+                __builtin_nontemporal_store(py, P.py + p0 + lane);
+            } else {
+                if (shifts) {
+                    (P.x + p0)[lane] = x;
+                    (P.y + p0)[lane] = y;
+                }
+                (P.px + p0)[lane] = px;
+                (P.py + p0)[lane] = py;
             }
-            wp = wn;
-            lf = lfn;
+            if constexpr (SIX)
+                if (shifts) (P.sigma + p0)[lane] = sg;
+            if constexpr (LINE && KICK) (P.psigma + p0)[lane] = psg;
+        }
+        if constexpr (DEPOSIT) {
+            cnt += __popcll(__ballot(hit));
+        }
+        if constexpr (NT) {
+            cur = ahead;
+            ahead = next;
+        } else {
+            cur = next;
         }
     }
 
     if constexpr (DEPOSIT) {
-        // combine the lanes' boxes and counts, then copy the box of tile cells
+        // combine the waves' boxes and counts, then copy the box of tile cells
         // to this workgroup's slice of the partials in 16-byte chunks (the
         // extra cells of the end chunks are zero and masked by the reader)
-        bi0 = wave_min(bi0);
-        bi1 = wave_max(bi1);
-        bj0 = wave_min(bj0);
-        bj1 = wave_max(bj1);
-        cnt = wave_sum(cnt);
-        if ((threadIdx.x & (kWave - 1)) == 0) {
-            atomicMin(&s_box[0], bi0);
-            atomicMax(&s_box[1], bi1);
-            atomicMin(&s_box[2], bj0);
-            atomicMax(&s_box[3], bj1);
+        lo = wave_pair_min(lo);
+        hi = wave_pair_max(hi);
+        if ((threadIdx.x & (kWave - 1)) == 0 && cnt) {
+            if (lo <= hi) {  // some cell of the tile (else lo is still all ones)
+                atomicMin(&s_box[0], (int)(lo & 0xffffu));
+                atomicMax(&s_box[1], (int)(hi & 0xffffu) + 1);
+                atomicMin(&s_box[2], (int)(lo >> 16));
+                atomicMax(&s_box[3], (int)(hi >> 16) + 1);
+            }
             atomicAdd(&s_count, cnt);
         }
         __syncthreads();
@@ -899,47 +1036,65 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     }
 }
 
-// NT: the streamed form (four-dimensional passes only).
-template <typename TE, bool KICK, bool DEPOSIT, bool SIX, bool NT = false>
+// FORM: 0, 8 (streamed, four-dimensional passes only) or 16 (the whole grid as
+// the tile, depositing passes only).  FIRST: the pass's first element, when it
+// is a linear map (four-dimensional passes only).
+template <typename TE, bool KICK, bool DEPOSIT, bool SIX, int FORM = 0, int FIRST = 0>
 __global__ void __launch_bounds__(1024)
     k_pass(ParticlePtrs P, GridGeom g, const TE *__restrict__ ef, double kappa,
            PassElements els, DepositTarget dep, unsigned lds_bytes)
 {
-    pass_body<TE, KICK, DEPOSIT, (SIX ? 1 : 0) | (NT ? 8 : 0)>(
+    pass_body<TE, KICK, DEPOSIT, (SIX ? 1 : 0) | FORM, FIRST>(
         P, g, ef, kappa, els, dep, lds_bytes, (int)blockIdx.x, (int)gridDim.x, LineSpec{});
 }
 
 // The pass with the B-spline field (phi: the node potential on nodes -1..nx
 // by -1..ny).
-template <typename TE, bool KICK, bool DEPOSIT, bool SIX>
+template <typename TE, bool KICK, bool DEPOSIT, bool SIX, int FORM = 0, int FIRST = 0>
 __global__ void __launch_bounds__(1024)
     k_pass_bspline(ParticlePtrs P, GridGeom g, const TE *__restrict__ phi, double kappa,
                    PassElements els, DepositTarget dep, unsigned lds_bytes)
 {
-    pass_body<TE, KICK, DEPOSIT, 4 | (SIX ? 1 : 0)>(P, g, phi, kappa, els, dep, lds_bytes,
-                                                    (int)blockIdx.x, (int)gridDim.x, LineSpec{});
+    pass_body<TE, KICK, DEPOSIT, 4 | (SIX ? 1 : 0) | FORM, FIRST>(
+        P, g, phi, kappa, els, dep, lds_bytes, (int)blockIdx.x, (int)gridDim.x, LineSpec{});
 }
 
 // The pass of a long bunch with its line density (six-dimensional).
-template <typename TE, bool KICK, bool DEPOSIT>
+template <typename TE, bool KICK, bool DEPOSIT, int FORM = 0>
 __global__ void __launch_bounds__(1024)
     k_pass_line(ParticlePtrs P, GridGeom g, const TE *__restrict__ ef, double kappa,
                 PassElements els, DepositTarget dep, unsigned lds_bytes, LineSpec line)
 {
-    pass_body<TE, KICK, DEPOSIT, 2>(P, g, ef, kappa, els, dep, lds_bytes, (int)blockIdx.x,
-                                    (int)gridDim.x, line);
+    pass_body<TE, KICK, DEPOSIT, 2 | FORM, 0>(P, g, ef, kappa, els, dep, lds_bytes, (int)blockIdx.x,
+                                       (int)gridDim.x, line);
+}
+
+// A pointer read from a table in memory, known to point to global memory (the
+// compiler otherwise takes it for one that might point to LDS, whose accesses
+// both memory counters must wait for).
+template <typename T>
+__device__ __forceinline__ T *global_memory(T *p)
+{
+    return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
 }
 
 // One pass over every beam of a batch: workgroup -> beam from the batch's
 // table, then the same body on that beam's particles, grid, field and
 // partials with its own kick strength and elements (steps[beam]).
-template <typename TE, bool KICK, bool DEPOSIT, bool SIX, bool NT = false>
+template <typename TE, bool KICK, bool DEPOSIT, bool SIX, int FORM = 0, int FIRST = 0>
 __global__ void __launch_bounds__(1024)
     k_pass_batched(BatchLaunch b, ParticlePtrs all, const BatchStep *__restrict__ steps,
                    unsigned lds_bytes)
 {
     const int k = b.pass_inst[blockIdx.x];
-    const BatchInstance &I = b.inst[k];
+    // copies: a reference into the table would be read again after every store
+    const BatchInstance I = b.inst[k];
+    const double kappa = steps[k].kappa;
+    DepositTarget dep;
+    dep.partial = global_memory(I.dep.partial);
+    dep.header = global_memory(I.dep.header);
+    dep.carry = global_memory(I.dep.carry);
+    dep.max_blocks = I.dep.max_blocks;
     ParticlePtrs P;
     P.x = all.x + I.p0;
     P.px = all.px + I.p0;
@@ -950,9 +1105,9 @@ __global__ void __launch_bounds__(1024)
     P.w = all.w ? all.w + I.p0 : nullptr;
     P.lost = all.lost ? all.lost + I.p0 : nullptr;
     P.n = I.n;
-    P.stream = NT;
-    pass_body<TE, KICK, DEPOSIT, (SIX ? 1 : 0) | (NT ? 8 : 0)>(
-        P, I.g, (const TE *)I.ef, steps[k].kappa, steps[k].els, I.dep, lds_bytes,
+    P.stream = (FORM & 8) != 0;
+    pass_body<TE, KICK, DEPOSIT, (SIX ? 1 : 0) | FORM, FIRST>(
+        P, I.g, global_memory((const TE *)I.ef), kappa, steps[k].els, dep, lds_bytes,
         (int)blockIdx.x - I.pass_block0, I.pass_blocks, LineSpec{});
 }
 
@@ -983,71 +1138,104 @@ size_t lds_budget()
     return SIX ? g_lds_limit6 : g_lds_limit;
 }
 
-template <typename TE, bool KICK, bool DEPOSIT, bool SIX, bool NT = false>
+template <typename TE, bool KICK, bool DEPOSIT, bool SIX, int FORM = 0, int FIRST = 0>
 hipError_t launch_pass_t(hipStream_t s, const ParticlePtrs &p, const GridGeom &g, const void *ef,
                          double kappa, const PassElements &els, const DepositTarget &dep,
                          int blocks, int threads)
 {
     const size_t lds = (KICK || DEPOSIT) ? lds_budget<SIX>() : 0;
-    hipLaunchKernelGGL((k_pass<TE, KICK, DEPOSIT, SIX, NT>), dim3(blocks), dim3(threads), lds, s,
-                       p, g, (const TE *)ef, kappa, els, dep, (unsigned)lds);
+    hipLaunchKernelGGL((k_pass<TE, KICK, DEPOSIT, SIX, FORM, FIRST>), dim3(blocks), dim3(threads),
+                       lds, s, p, g, (const TE *)ef, kappa, els, dep, (unsigned)lds);
     return hipGetLastError();
 }
 
-template <typename TE, bool KICK, bool DEPOSIT, bool SIX>
+template <typename TE, bool KICK, bool DEPOSIT, bool SIX, int FORM = 0, int FIRST = 0>
 hipError_t launch_pass_bspline_t(hipStream_t s, const ParticlePtrs &p, const GridGeom &g,
                                  const void *phi, double kappa, const PassElements &els,
                                  const DepositTarget &dep, int blocks, int threads)
 {
-    const size_t lds = DEPOSIT ? lds_budget<SIX>() : 0;
-    hipLaunchKernelGGL((k_pass_bspline<TE, KICK, DEPOSIT, SIX>), dim3(blocks), dim3(threads), lds,
-                       s, p, g, (const TE *)phi, kappa, els, dep, (unsigned)lds);
+    const size_t lds = lds_budget<SIX>();
+    hipLaunchKernelGGL((k_pass_bspline<TE, KICK, DEPOSIT, SIX, FORM, FIRST>), dim3(blocks),
+                       dim3(threads), lds, s, p, g, (const TE *)phi, kappa, els, dep,
+                       (unsigned)lds);
     return hipGetLastError();
 }
 
-template <typename TE, bool KICK, bool DEPOSIT>
+template <typename TE, bool KICK, bool DEPOSIT, int FORM = 0>
 hipError_t launch_pass_line_t(hipStream_t s, const ParticlePtrs &p, const GridGeom &g,
                               const void *ef, double kappa, const PassElements &els,
                               const DepositTarget &dep, int blocks, int threads,
                               const LineSpec &line)
 {
-    hipLaunchKernelGGL((k_pass_line<TE, KICK, DEPOSIT>), dim3(blocks), dim3(threads), g_lds_limit6,
-                       s, p, g, (const TE *)ef, kappa, els, dep, (unsigned)g_lds_limit6, line);
+    hipLaunchKernelGGL((k_pass_line<TE, KICK, DEPOSIT, FORM>), dim3(blocks), dim3(threads),
+                       g_lds_limit6, s, p, g, (const TE *)ef, kappa, els, dep,
+                       (unsigned)g_lds_limit6, line);
     return hipGetLastError();
 }
 
-template <typename TE, bool KICK, bool DEPOSIT, bool SIX, bool NT = false>
+template <typename TE, bool KICK, bool DEPOSIT, bool SIX, int FORM = 0, int FIRST = 0>
 hipError_t launch_pass_batched_t(hipStream_t s, const BatchLaunch &b, const ParticlePtrs &all,
                                  const BatchStep *steps, int blocks, int threads)
 {
     const size_t lds = (KICK || DEPOSIT) ? lds_budget<SIX>() : 0;
-    hipLaunchKernelGGL((k_pass_batched<TE, KICK, DEPOSIT, SIX, NT>), dim3(blocks), dim3(threads),
-                       lds, s, b, all, steps, (unsigned)lds);
+    hipLaunchKernelGGL((k_pass_batched<TE, KICK, DEPOSIT, SIX, FORM, FIRST>), dim3(blocks),
+                       dim3(threads), lds, s, b, all, steps, (unsigned)lds);
     return hipGetLastError();
 }
 
-template <typename TE, bool SIX>
-void pass_kernels_of(std::vector<const void *> &out)
+// Calls f with the integral constants of a pass's form and, for the passes of
+// a steady turn, of its resident first element.
+template <typename F>
+hipError_t with_form(bool whole, bool stream, F &&f)
 {
-    out.push_back((const void *)k_pass<TE, true, true, SIX>);
-    out.push_back((const void *)k_pass<TE, false, true, SIX>);
-    out.push_back((const void *)k_pass<TE, true, false, SIX>);
-    out.push_back((const void *)k_pass_batched<TE, true, true, SIX>);
-    out.push_back((const void *)k_pass_batched<TE, false, true, SIX>);
-    out.push_back((const void *)k_pass_batched<TE, true, false, SIX>);
-    out.push_back((const void *)k_pass_bspline<TE, true, true, SIX>);
-    if (!SIX) {
-        out.push_back((const void *)k_pass<TE, true, true, false, true>);
-        out.push_back((const void *)k_pass<TE, false, true, false, true>);
-        out.push_back((const void *)k_pass<TE, true, false, false, true>);
-        out.push_back((const void *)k_pass_batched<TE, true, true, false, true>);
-        out.push_back((const void *)k_pass_batched<TE, false, true, false, true>);
-        out.push_back((const void *)k_pass_batched<TE, true, false, false, true>);
+    if (whole) return f(std::integral_constant<int, 16>{});
+    if (stream) return f(std::integral_constant<int, 8>{});
+    return f(std::integral_constant<int, 0>{});
+}
+template <typename F>
+hipError_t with_first(int first, F &&f)
+{
+    if (first == SCPIC_EL_LIN2X2) return f(std::integral_constant<int, SCPIC_EL_LIN2X2>{});
+    if (first == SCPIC_EL_LIN4X4) return f(std::integral_constant<int, SCPIC_EL_LIN4X4>{});
+    return f(std::integral_constant<int, 0>{});
+}
+
+// The kernels of one form that use LDS.
+template <typename TE, int FORM, int FIRST>
+void steady_kernels_of(std::vector<const void *> &out)
+{
+    out.push_back((const void *)k_pass<TE, true, true, false, FORM, FIRST>);
+    out.push_back((const void *)k_pass_batched<TE, true, true, false, FORM, FIRST>);
+    if constexpr (FORM != 8)
+        out.push_back((const void *)k_pass_bspline<TE, true, true, false, FORM, FIRST>);
+}
+template <typename TE, int FORM>
+void form_kernels_of(std::vector<const void *> &four, std::vector<const void *> &six)
+{
+    steady_kernels_of<TE, FORM, 0>(four);
+    steady_kernels_of<TE, FORM, SCPIC_EL_LIN2X2>(four);
+    steady_kernels_of<TE, FORM, SCPIC_EL_LIN4X4>(four);
+    four.push_back((const void *)k_pass<TE, false, true, false, FORM>);
+    four.push_back((const void *)k_pass_batched<TE, false, true, false, FORM>);
+    if constexpr (FORM != 16) {
+        four.push_back((const void *)k_pass<TE, true, false, false, FORM>);
+        four.push_back((const void *)k_pass_batched<TE, true, false, false, FORM>);
     }
-    if (SIX) {
-        out.push_back((const void *)k_pass_line<TE, true, true>);
-        out.push_back((const void *)k_pass_line<TE, false, true>);
-        out.push_back((const void *)k_pass_line<TE, true, false>);
+    if constexpr (FORM != 8) {
+        six.push_back((const void *)k_pass<TE, true, true, true, FORM>);
+        six.push_back((const void *)k_pass<TE, false, true, true, FORM>);
+        six.push_back((const void *)k_pass_batched<TE, true, true, true, FORM>);
+        six.push_back((const void *)k_pass_batched<TE, false, true, true, FORM>);
+        six.push_back((const void *)k_pass_bspline<TE, true, true, true, FORM>);
+        six.push_back((const void *)k_pass_line<TE, true, true, FORM>);
+        six.push_back((const void *)k_pass_line<TE, false, true, FORM>);
+    }
+    if constexpr (FORM == 0) {
+        four.push_back((const void *)k_pass_bspline<TE, true, false, false>);
+        six.push_back((const void *)k_pass<TE, true, false, true>);
+        six.push_back((const void *)k_pass_batched<TE, true, false, true>);
+        six.push_back((const void *)k_pass_bspline<TE, true, false, true>);
+        six.push_back((const void *)k_pass_line<TE, true, false>);
     }
 }
 
@@ -1060,6 +1248,12 @@ bool has_thick(const PassElements &els)
     return false;
 }
 
+int first_linear(const PassElements &els)
+{
+    if (els.n_el < 1) return 0;
+    return els.kind[0] == SCPIC_EL_LIN2X2 || els.kind[0] == SCPIC_EL_LIN4X4 ? els.kind[0] : 0;
+}
+
 // Allow the passes the dynamic LDS they use (beyond the default limit): the
 // device's per-workgroup LDS (lds_per_workgroup) minus the kernels' static
 // LDS, at most 256 bytes for the four-dimensional passes and kPassStaticLds
@@ -1070,10 +1264,12 @@ hipError_t prepare_pass_kernels(size_t lds_per_workgroup)
     g_lds_limit = lds_per_workgroup - 256;
     g_lds_limit6 = lds_per_workgroup - kPassStaticLds;
     std::vector<const void *> four, six;
-    pass_kernels_of<double, false>(four);
-    pass_kernels_of<float, false>(four);
-    pass_kernels_of<double, true>(six);
-    pass_kernels_of<float, true>(six);
+    form_kernels_of<double, 0>(four, six);
+    form_kernels_of<double, 8>(four, six);
+    form_kernels_of<double, 16>(four, six);
+    form_kernels_of<float, 0>(four, six);
+    form_kernels_of<float, 8>(four, six);
+    form_kernels_of<float, 16>(four, six);
     for (const void *k : four) {
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)g_lds_limit);
@@ -1087,30 +1283,143 @@ hipError_t prepare_pass_kernels(size_t lds_per_workgroup)
     return hipSuccess;
 }
 
-// The runtime flags as template arguments: L(TE, KICK, DEPOSIT, SIX) expands
-// to the launch of the matching instantiation.
-#define SCPIC_DISPATCH(L)                                                                     \
-    if (mixed) {                                                                              \
-        if (six)                                                                              \
-            return kick ? (deposit ? L(float, true, true, true) : L(float, true, false, true)) \
-                        : (deposit ? L(float, false, true, true)                              \
-                                   : L(float, false, false, true));                           \
-        return kick ? (deposit ? L(float, true, true, false) : L(float, true, false, false))  \
-                    : (deposit ? L(float, false, true, false) : L(float, false, false, false)); \
-    }                                                                                         \
-    if (six)                                                                                  \
-        return kick ? (deposit ? L(double, true, true, true) : L(double, true, false, true))  \
-                    : (deposit ? L(double, false, true, true) : L(double, false, false, true)); \
-    return kick ? (deposit ? L(double, true, true, false) : L(double, true, false, false))    \
-                : (deposit ? L(double, false, true, false) : L(double, false, false, false))
+// Whether a depositing pass takes the whole grid as its tile: when it fits in
+// LDS and each of the nblk * threads lanes has few particles.  The other form's
+// set-up (the header's read, then the field box moved into LDS) is about 1 us
+// and its gathers then take no part in the L2's traffic.  Four-dimensional
+// passes on 128^2, FP64, us per step, whole grid and staged box: 24.0, 24.6 at
+// one particle per lane, 27.5, 27.6 at two, 29.7, 28.7 at three, 31.7, 30.1 at
+// four.  The six-dimensional passes are bound by instruction issue and hide the
+// gathers: 28.1, 28.9 at four (1.04e6 particles), 68.5, 70.3 at eight, 106.3,
+// 108.9 at sixteen.
+bool whole_tile(const GridGeom &g, int64_t n, int nblk, int threads, bool six, size_t other_lds)
+{
+    const int64_t most_per_lane = six ? 16 : 2;
+    return sizeof(uint32_t) * (size_t)g.nx * g.ny + other_lds <= pass_lds(six) &&
+           n <= most_per_lane * nblk * threads;
+}
 
-// The four-dimensional kernels by precision, kick and deposit.
-#define SCPIC_DISPATCH4(L)                                                                \
-    if (mixed)                                                                            \
-        return kick ? (deposit ? L(float, true, true) : L(float, true, false))            \
-                    : (deposit ? L(float, false, true) : L(float, false, false));         \
-    return kick ? (deposit ? L(double, true, true) : L(double, true, false))              \
-                : (deposit ? L(double, false, true) : L(double, false, false))
+namespace {
+
+template <typename TE>
+hipError_t launch_pass_of(hipStream_t s, const ParticlePtrs &p, const GridGeom &g, bool kick,
+                          const void *ef, double kappa, const PassElements &els, bool deposit,
+                          const DepositTarget &dep, int blocks, int threads, const LineSpec *line,
+                          const void *phi)
+{
+    const bool six = has_thick(els) || (line && (kick || deposit));
+    // LDS of the element parameters and the line histogram beside the tile
+    const size_t other = sizeof(els.p) + (line ? 4 * (size_t)line->nz + 16 : 0);
+    const bool whole = deposit && whole_tile(g, p.n, blocks, threads, six, other);
+    if (phi && kick) {
+        if (!deposit)
+            return six ? launch_pass_bspline_t<TE, true, false, true>(s, p, g, phi, kappa, els, dep,
+                                                                      blocks, threads)
+                       : launch_pass_bspline_t<TE, true, false, false>(s, p, g, phi, kappa, els,
+                                                                       dep, blocks, threads);
+        return with_form(whole, false, [&](auto form) {
+            constexpr int FORM = decltype(form)::value;
+            if constexpr (FORM != 8) {
+                if (six)
+                    return launch_pass_bspline_t<TE, true, true, true, FORM>(
+                        s, p, g, phi, kappa, els, dep, blocks, threads);
+                return with_first(first_linear(els), [&](auto first) {
+                    return launch_pass_bspline_t<TE, true, true, false, FORM,
+                                                 decltype(first)::value>(s, p, g, phi, kappa, els,
+                                                                         dep, blocks, threads);
+                });
+            }
+            return hipErrorInvalidValue;
+        });
+    }
+    if (line && (kick || deposit)) {
+        if (!deposit)
+            return launch_pass_line_t<TE, true, false>(s, p, g, ef, kappa, els, dep, blocks,
+                                                       threads, *line);
+        return with_form(whole, false, [&](auto form) {
+            constexpr int FORM = decltype(form)::value;
+            if constexpr (FORM != 8)
+                return kick ? launch_pass_line_t<TE, true, true, FORM>(s, p, g, ef, kappa, els, dep,
+                                                                       blocks, threads, *line)
+                            : launch_pass_line_t<TE, false, true, FORM>(
+                                  s, p, g, ef, kappa, els, dep, blocks, threads, *line);
+            return hipErrorInvalidValue;
+        });
+    }
+    if (!deposit) {
+        if (six)
+            return kick ? launch_pass_t<TE, true, false, true>(s, p, g, ef, kappa, els, dep, blocks,
+                                                               threads)
+                        : launch_pass_t<TE, false, false, true>(s, p, g, ef, kappa, els, dep,
+                                                                blocks, threads);
+        return with_form(false, p.stream, [&](auto form) {
+            constexpr int FORM = decltype(form)::value;
+            if constexpr (FORM != 16)
+                return kick ? launch_pass_t<TE, true, false, false, FORM>(s, p, g, ef, kappa, els,
+                                                                          dep, blocks, threads)
+                            : launch_pass_t<TE, false, false, false, FORM>(
+                                  s, p, g, ef, kappa, els, dep, blocks, threads);
+            return hipErrorInvalidValue;
+        });
+    }
+    return with_form(whole, p.stream && !six, [&](auto form) {
+        constexpr int FORM = decltype(form)::value;
+        if constexpr (FORM != 8)
+            if (six)
+                return kick ? launch_pass_t<TE, true, true, true, FORM>(s, p, g, ef, kappa, els,
+                                                                        dep, blocks, threads)
+                            : launch_pass_t<TE, false, true, true, FORM>(s, p, g, ef, kappa, els,
+                                                                         dep, blocks, threads);
+        if (!kick)
+            return launch_pass_t<TE, false, true, false, FORM>(s, p, g, ef, kappa, els, dep, blocks,
+                                                               threads);
+        return with_first(first_linear(els), [&](auto first) {
+            return launch_pass_t<TE, true, true, false, FORM, decltype(first)::value>(
+                s, p, g, ef, kappa, els, dep, blocks, threads);
+        });
+    });
+}
+
+template <typename TE>
+hipError_t launch_pass_batched_of(hipStream_t s, const BatchLaunch &b, const ParticlePtrs &all,
+                                  const BatchStep *steps, bool kick, bool deposit,
+                                  const BatchPassForm &f, int blocks, int threads)
+{
+    if (!deposit) {
+        if (f.six)
+            return kick ? launch_pass_batched_t<TE, true, false, true>(s, b, all, steps, blocks,
+                                                                       threads)
+                        : launch_pass_batched_t<TE, false, false, true>(s, b, all, steps, blocks,
+                                                                        threads);
+        return with_form(false, all.stream, [&](auto form) {
+            constexpr int FORM = decltype(form)::value;
+            if constexpr (FORM != 16)
+                return kick ? launch_pass_batched_t<TE, true, false, false, FORM>(
+                                  s, b, all, steps, blocks, threads)
+                            : launch_pass_batched_t<TE, false, false, false, FORM>(
+                                  s, b, all, steps, blocks, threads);
+            return hipErrorInvalidValue;
+        });
+    }
+    return with_form(f.whole, all.stream && !f.six, [&](auto form) {
+        constexpr int FORM = decltype(form)::value;
+        if constexpr (FORM != 8)
+            if (f.six)
+                return kick ? launch_pass_batched_t<TE, true, true, true, FORM>(s, b, all, steps,
+                                                                                blocks, threads)
+                            : launch_pass_batched_t<TE, false, true, true, FORM>(s, b, all, steps,
+                                                                                 blocks, threads);
+        if (!kick)
+            return launch_pass_batched_t<TE, false, true, false, FORM>(s, b, all, steps, blocks,
+                                                                       threads);
+        return with_first(f.first, [&](auto first) {
+            return launch_pass_batched_t<TE, true, true, false, FORM, decltype(first)::value>(
+                s, b, all, steps, blocks, threads);
+        });
+    });
+}
+
+}  // namespace
 
 hipError_t launch_pass(hipStream_t s, const ParticlePtrs &p, const GridGeom &g, bool kick,
                        bool mixed, const void *ef, double kappa, const PassElements &els,
@@ -1118,57 +1427,24 @@ hipError_t launch_pass(hipStream_t s, const ParticlePtrs &p, const GridGeom &g, 
                        const LineSpec *line, const void *bspline_phi)
 {
     if (blocks <= 0) return hipSuccess;
-    if (bspline_phi && kick) {
-        const bool six = has_thick(els);
-#define SCPIC_LB(T, D, S) \
-    launch_pass_bspline_t<T, true, D, S>(s, p, g, bspline_phi, kappa, els, dep, blocks, threads)
-        if (mixed)
-            return six ? (deposit ? SCPIC_LB(float, true, true) : SCPIC_LB(float, false, true))
-                       : (deposit ? SCPIC_LB(float, true, false) : SCPIC_LB(float, false, false));
-        return six ? (deposit ? SCPIC_LB(double, true, true) : SCPIC_LB(double, false, true))
-                   : (deposit ? SCPIC_LB(double, true, false) : SCPIC_LB(double, false, false));
-#undef SCPIC_LB
-    }
-    if (line && (kick || deposit)) {
-#define SCPIC_LL(T)                                                                             \
-    (kick ? (deposit ? launch_pass_line_t<T, true, true>(s, p, g, ef, kappa, els, dep, blocks,  \
-                                                         threads, *line)                        \
-                     : launch_pass_line_t<T, true, false>(s, p, g, ef, kappa, els, dep, blocks, \
-                                                          threads, *line))                      \
-          : launch_pass_line_t<T, false, true>(s, p, g, ef, kappa, els, dep, blocks, threads,   \
-                                               *line))
-        return mixed ? SCPIC_LL(float) : SCPIC_LL(double);
-#undef SCPIC_LL
-    }
-    const bool six = has_thick(els);
-    if (!six && p.stream) {
-#define SCPIC_L(T, K, D) \
-    launch_pass_t<T, K, D, false, true>(s, p, g, ef, kappa, els, dep, blocks, threads)
-        SCPIC_DISPATCH4(SCPIC_L);
-#undef SCPIC_L
-    }
-#define SCPIC_L(T, K, D, S) launch_pass_t<T, K, D, S>(s, p, g, ef, kappa, els, dep, blocks, threads)
-    SCPIC_DISPATCH(SCPIC_L);
-#undef SCPIC_L
+    return mixed ? launch_pass_of<float>(s, p, g, kick, ef, kappa, els, deposit, dep, blocks,
+                                         threads, line, bspline_phi)
+                 : launch_pass_of<double>(s, p, g, kick, ef, kappa, els, deposit, dep, blocks,
+                                          threads, line, bspline_phi);
 }
 
 hipError_t launch_pass_batched(hipStream_t s, const BatchLaunch &b, const ParticlePtrs &all,
                                const BatchStep *steps, bool kick, bool mixed, bool deposit,
-                               bool six, int blocks, int threads)
+                               const BatchPassForm &form, int blocks, int threads)
 {
     if (blocks <= 0) return hipSuccess;
-    if (!six && all.stream) {
-#define SCPIC_L(T, K, D) \
-    launch_pass_batched_t<T, K, D, false, true>(s, b, all, steps, blocks, threads)
-        SCPIC_DISPATCH4(SCPIC_L);
-#undef SCPIC_L
-    }
-#define SCPIC_L(T, K, D, S) launch_pass_batched_t<T, K, D, S>(s, b, all, steps, blocks, threads)
-    SCPIC_DISPATCH(SCPIC_L);
-#undef SCPIC_L
+    return mixed ? launch_pass_batched_of<float>(s, b, all, steps, kick, deposit, form, blocks,
+                                                 threads)
+                 : launch_pass_batched_of<double>(s, b, all, steps, kick, deposit, form, blocks,
+                                                  threads);
 }
-#undef SCPIC_DISPATCH
-#undef SCPIC_DISPATCH4
+
+size_t pass_lds(bool six) { return six ? g_lds_limit6 : g_lds_limit; }
 
 namespace {
 

@@ -78,7 +78,7 @@ struct scpic_ctx {
     int n_cu = 0;
     int max_blocks = 0;
     int pass_blocks = 0;  // 0 = automatic
-    int pass_threads = 1024;
+    int pass_threads = 0;  // 0 = automatic
     bool use_graph = true;
     int last_deposit_blocks = 0;
 
@@ -205,6 +205,17 @@ ParticlePtrs to_ptrs(const scpic_particles *p)
     return r;
 }
 
+// Threads per workgroup of a pass over n particles.  Automatic: 512 while no
+// workgroup then has a second round, so that a small beam spreads over more
+// compute units (FP64 us per step: 1e4 particles on 64^2 17.0 with 1024 threads,
+// 15.8 with 512, 16.1 with 256; 6.5e4 on 128^2 20.6, 19.8, 20.6; 1e5 21.1, 20.6,
+// 20.6); 1024 from there on, where waves count (1e6: 29.8, 31.5 with 512).
+int threads_for(const scpic_ctx *c, int64_t n)
+{
+    if (c->pass_threads > 0) return c->pass_threads;
+    return n <= (int64_t)512 * c->n_cu ? 512 : 1024;
+}
+
 // Workgroups of a pass over n particles.  A pass that kicks or deposits runs
 // the depositing passes' count (one per compute unit unless set): workgroup b
 // then owns the same particles as in the deposit that wrote header b, whose
@@ -213,7 +224,8 @@ ParticlePtrs to_ptrs(const scpic_particles *p)
 int blocks_for(const scpic_ctx *c, int64_t n, bool lds_pass)
 {
     if (n <= 0) return 0;
-    const int64_t need = (n + c->pass_threads - 1) / c->pass_threads;
+    const int threads = threads_for(c, n);
+    const int64_t need = (n + threads - 1) / threads;
     const int64_t cap = lds_pass ? (c->pass_blocks > 0 ? c->pass_blocks : c->n_cu)
                                  : (int64_t)c->n_cu * 8;
     return (int)std::max<int64_t>(1, std::min<int64_t>(need, std::min<int64_t>(cap, c->max_blocks)));
@@ -390,7 +402,7 @@ scpic_status enqueue_pass(scpic_ctx *c, hipStream_t s, const scpic_particles *pa
         !per_element && c->line.nz > 0 && (op.kick || op.deposit) ? &c->line : nullptr;
     const void *bphi = !per_element && c->bspline && op.kick ? c->sw.phi : nullptr;
     hipError_t e = launch_pass(s, to_ptrs(parts), c->geom, op.kick, c->mixed, c->ef, op.kappa,
-                               op.els, op.deposit, c->dep, blocks, c->pass_threads, line, bphi);
+                               op.els, op.deposit, c->dep, blocks, threads_for(c, parts->n), line, bphi);
     if (e != hipSuccess) return fail_hip(e, "particle pass launch");
     if (op.deposit) c->last_deposit_blocks = blocks;
     return SCPIC_OK;
@@ -1096,6 +1108,7 @@ struct BatchSchedule {
     std::vector<unsigned char> key;
     std::vector<PassOp> shape;     // kick / deposit per op (kappa, els unused)
     std::vector<char> six;         // per op: some beam's elements are thick
+    std::vector<char> first;       // per op: first_linear of every beam's elements, else 0
     BatchStep *steps = nullptr;    // device [n_ops][n_inst]
     hipGraphExec_t exec = nullptr;
     uint64_t last_use = 0;
@@ -1448,6 +1461,12 @@ scpic_status batch_schedule(scpic_batch *b, const std::vector<std::vector<PassOp
     for (size_t j = 0; j < n_ops; ++j)
         for (size_t k = 0; k < n; ++k)
             if (has_thick(ops[k][j].els)) s.six[j] = 1;
+    s.first.assign(n_ops, 0);
+    for (size_t j = 0; j < n_ops; ++j) {
+        s.first[j] = (char)first_linear(ops[0][j].els);
+        for (size_t k = 1; k < n; ++k)
+            if (first_linear(ops[k][j].els) != s.first[j]) s.first[j] = 0;
+    }
     hipError_t e = hipMalloc(&s.steps, sizeof(BatchStep) * std::max<size_t>(1, table.size()));
     if (e != hipSuccess) return fail(SCPIC_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
     if (!table.empty()) {
@@ -1469,9 +1488,17 @@ scpic_status batch_enqueue(scpic_batch *b, hipStream_t s, const scpic_particles 
     const ParticlePtrs all = to_ptrs(parts);
     for (size_t j = 0; j < sch.shape.size(); ++j) {
         const PassOp &op = sch.shape[j];
+        BatchPassForm form;
+        form.six = sch.six[j] != 0;
+        form.first = sch.first[j];
+        form.whole = true;
+        for (const BatchInstance &I : b->inst)
+            if (I.pass_blocks > 0 && !whole_tile(I.g, I.n, I.pass_blocks, b->pass_threads,
+                                                 form.six, sizeof(PassElements::p)))
+                form.whole = false;
         hipError_t e = launch_pass_batched(s, b->launch, all, sch.steps + j * b->n_inst, op.kick,
-                                           b->mixed, op.deposit, sch.six[j] != 0,
-                                           b->total_pass_blocks, b->pass_threads);
+                                           b->mixed, op.deposit, form, b->total_pass_blocks,
+                                           b->pass_threads);
         if (e != hipSuccess) return fail_hip(e, "batched pass launch");
         if (op.deposit) {
             e = launch_solve_batched(s, b->launch, b->mixed, b->shape);

@@ -54,6 +54,24 @@ struct GridGeom {
     double x_min, y_min, inv_dx, inv_dy;
 };
 
+// Cell index i and 12-bit fraction a (0..4096) of node coordinate t in [0, 2^17):
+// i = floor(t), a = floor((t - i) 4096 + 0.5), each operation rounded to
+// nearest, evaluated as one conversion: 8192 t, exact, truncated to an integer
+// v = 8192 i + floor(8192 (t - i)), and a = floor((floor(2 u) + 1) / 2) =
+// floor(u + 0.5) for u = 4096 (t - i).  The two agree wherever u + 0.5 is
+// exact in 53 bits, which it is for u >= 0.5 (the sum's last place is not
+// above u's) and, below 0.5, for every u but 0.5 - 2^-54: there the rounded
+// sum is 1, so a = 1.  Adding 2^-54 to 8192 t gives that one value (a tie,
+// 1 - 2^-53 -> 1) and leaves every other in its integer interval: it is under
+// half a unit of the last place from 2^-1 on but for the tie, and cannot reach
+// 1 from below 2^-1.  16 FP64 and conversion operations become 4.
+__host__ __device__ inline void cell_fraction(double t, int &i, int &a)
+{
+    const int v = (int)__builtin_fma(t, 8192.0, 0x1p-54);
+    i = v >> 13;
+    a = ((v & 8191) + 1) >> 1;
+}
+
 // Elements of one pass, passed by value in the kernel arguments (read with
 // scalar loads, uniform across the wave).  A thick quadrupole's p[3..8] hold
 // values derived on the host from k1 and L: phi0 = sqrt|k1| L, sin, cos,
@@ -216,12 +234,29 @@ hipError_t prepare_pass_kernels(size_t lds_per_workgroup);
 // True when els holds a thick element (the pass then needs sigma, p_sigma).
 bool has_thick(const PassElements &els);
 
+// The kind of els' first element when that is a linear map, else 0 (the passes
+// that kick and deposit then keep its matrix in scalar registers).
+int first_linear(const PassElements &els);
+
+// Whether a depositing pass of nblk workgroups over n particles takes the
+// whole grid as its LDS tile (other_lds: what it holds in LDS beside the
+// tile); a pass's LDS budget.
+bool whole_tile(const GridGeom &g, int64_t n, int nblk, int threads, bool six, size_t other_lds);
+size_t pass_lds(bool six);
+
+// What every beam's part of one batched pass has in common: six when any
+// beam's elements are thick; whole when whole_tile holds for every beam; first:
+// first_linear of the elements when every beam's is the same, else 0.
+struct BatchPassForm {
+    bool six = false, whole = false;
+    int first = 0;
+};
+
 // One particle pass over every beam of a batch (blocks = total pass
-// workgroups of the batch); steps[beam] holds each beam's kick and elements;
-// six when any beam's elements in this pass are thick.
+// workgroups of the batch); steps[beam] holds each beam's kick and elements.
 hipError_t launch_pass_batched(hipStream_t s, const BatchLaunch &b, const ParticlePtrs &all,
                                const BatchStep *steps, bool kick, bool mixed, bool deposit,
-                               bool six, int blocks, int threads);
+                               const BatchPassForm &form, int blocks, int threads);
 
 // Exact charge grid q (int64) and deposited count from the partials of the
 // last depositing pass (blocks_used workgroups); clears the carry grid.

@@ -713,7 +713,7 @@ scpic_status create_impl(scpic_ctx *c, const scpic_grid *grid, int32_t precision
     ALLOC(c->sw.spec_a, ce * (size_t)(hy + 1) * nx);
     ALLOC(c->sw.spec_b, 2 * ce * (size_t)(hy + 1) * nx);
     ALLOC(c->ef, 2 * fe * ncell);
-    ALLOC(c->diag_part, sizeof(double) * kMomentBlocks * kMoments);
+    ALLOC(c->diag_part, sizeof(double) * 2 * kMomentBlocks * kMoments);
     ALLOC(c->diag_sums, sizeof(double) * 2 * kMoments);
 #undef ALLOC
     SCPIC_HIP_TRY(hipMemset(c->dep.carry, 0, sizeof(unsigned long long) * ncell), "hipMemset");

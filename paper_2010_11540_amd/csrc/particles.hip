@@ -125,12 +125,26 @@ __device__ __forceinline__ TE gather_scalar(const TE *u, int l00, int row, const
 }
 
 // Field at (x, y) in cell c (c.i, c.j from cic()) from the bicubic B-spline
-// surface of the node potential u (nodes -1..nx by -1..ny, row length ny + 2):
+// surface of the node potential u (nodes -1..nx by -1..ny):
 //   phi = sum_{m,n} u[i+m-1][j+n-1] B_m(tx) B_n(ty),  E = -grad phi,
 // with the uniform cubic basis B_m on the exact cell fractions (not the
-// 12-bit ones of the deposit); rows are contracted first.
+// 12-bit ones of the deposit); rows are contracted first.  v: the potential on
+// the cell's 4 x 4 nodes.
 template <typename TE>
-__device__ __forceinline__ void bspline_field(const GridGeom &g, const TE *__restrict__ u,
+struct SplineNodes {
+    TE v[4][4];
+    // base: node (i-1, j-1), row: the distance from row to row
+    __device__ __forceinline__ void load(const TE *base, int row)
+    {
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int n = 0; n < 4; ++n) v[m][n] = base[m * row + n];
+    }
+};
+
+template <typename TE>
+__device__ __forceinline__ void bspline_field(const GridGeom &g, const SplineNodes<TE> &u,
                                               double x, double y, const Cic &c, TE &fx, TE &fy)
 {
     const TE tx = (TE)((x - g.x_min) * g.inv_dx - (double)c.i);
@@ -149,18 +163,12 @@ __device__ __forceinline__ void bspline_field(const GridGeom &g, const TE *__res
     };
     basis(tx, bx, dbx);
     basis(ty, by, dby);
-    const int row = g.ny + 2;
-    const TE *base = u + (size_t)c.i * row + c.j;  // node (i-1, j-1)
-    TE v[4][4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int n = 0; n < 4; ++n) v[m][n] = base[m * row + n];
     TE sx = 0, sy = 0;
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-        const TE r = v[m][0] * by[0] + v[m][1] * by[1] + v[m][2] * by[2] + v[m][3] * by[3];
-        const TE d = v[m][0] * dby[0] + v[m][1] * dby[1] + v[m][2] * dby[2] + v[m][3] * dby[3];
+        const TE r = u.v[m][0] * by[0] + u.v[m][1] * by[1] + u.v[m][2] * by[2] + u.v[m][3] * by[3];
+        const TE d =
+            u.v[m][0] * dby[0] + u.v[m][1] * dby[1] + u.v[m][2] * dby[2] + u.v[m][3] * dby[3];
         sx = sx + dbx[m] * r;
         sy = sy + bx[m] * d;
     }
@@ -451,10 +459,13 @@ __device__ __forceinline__ int div_small(int t, int w, float inv_w)
 // j0..j0+w-1, row-major with row length w.
 struct Box {
     int i0, j0, h, w;
-    // the four nodes of cell (i, j) lie inside (h and w are at least 1)
+    // nodes (i, j) to (i + SPAN, j + SPAN) lie inside, for a cell the four
+    // nodes with SPAN 1 (h and w are at least SPAN)
+    template <int SPAN = 1>
     __device__ __forceinline__ bool holds_cell(int i, int j) const
     {
-        return ((uint32_t)(i - i0) < (uint32_t)(h - 1)) & ((uint32_t)(j - j0) < (uint32_t)(w - 1));
+        return ((uint32_t)(i - i0) < (uint32_t)(h - SPAN)) &
+               ((uint32_t)(j - j0) < (uint32_t)(w - SPAN));
     }
     __device__ __forceinline__ int at(int i, int j) const { return (i - i0) * w + (j - j0); }
 };
@@ -630,8 +641,9 @@ __device__ __forceinline__ void deposit_cell(uint32_t *lq, int l, int row,
 // previous pass's box and no field staging, only the zeroing of the tile.
 // Otherwise the tile covers the box the workgroup's
 // previous deposit recorded (its header; a workgroup owns the same particles
-// at every step of a track), and that box of the field, which holds every
-// node the kick gathers from, is staged in LDS beside the tile when it fits.
+// at every step of a track), and that box of the field (of the potential under
+// the B-spline gather), which holds every node the kick gathers from, is
+// staged in LDS beside the tile when it fits.
 // At the end each workgroup writes the bounding box of its tile cells to its
 // slice of the partials (no global atomics).
 //
@@ -725,22 +737,27 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     hd.j1 = -2;
     if ((KICK || DEPOSIT) && !WHOLE) hd = dep.header[bid];
     // The kick stages the field over the previous box (every node it gathers
-    // from) when that box fits in LDS beside the charge tile.  The staging
-    // moves units of 16 bytes, kUnitNodes nodes each: the box's columns are
-    // rounded out to whole units (ny is a multiple of 4), and 64 units of
-    // slack follow the box.
-    constexpr int kUnitNodes = 16 / (int)sizeof(V);
+    // from) when that box fits in LDS beside the charge tile: (Ex, Ey) of the
+    // box's nodes, or the potential on them and one node around (box indices
+    // count from node -1 then).  The staging moves units of 16 bytes (4 for the
+    // float potential, whose rows are not aligned to more), kUnitNodes nodes
+    // each: the box's columns are rounded out to whole units (a row of nodes,
+    // ny or ny + 2 of them, holds whole units), and 64 units of slack follow.
+    using S = std::conditional_t<BSPL, TE, V>;
+    constexpr int kUnitBytes = sizeof(S) == 4 ? 4 : 16;
+    constexpr int kUnitNodes = kUnitBytes / (int)sizeof(S);
+    constexpr int kSpan = BSPL ? 3 : 1;  // nodes a cell needs beyond its first, per axis
     const bool known = hd.i0 >= 0 && hd.i0 <= hd.i1 && hd.j0 >= 0 && hd.j0 <= hd.j1 &&
                        hd.i1 < g.nx && hd.j1 < g.ny;
-    Box fbox{0, 0, 1, 1};
+    Box fbox{0, 0, kSpan, kSpan};
     if (known) {
-        const int j0 = hd.j0 & ~(kUnitNodes - 1), j1 = hd.j1 | (kUnitNodes - 1);
-        fbox = Box{hd.i0, j0, hd.i1 - hd.i0 + 1, j1 - j0 + 1};
+        const int around = BSPL ? 2 : 0;
+        const int j0 = hd.j0 & ~(kUnitNodes - 1), j1 = (hd.j1 + around) | (kUnitNodes - 1);
+        fbox = Box{hd.i0, j0, hd.i1 + around - hd.i0 + 1, j1 - j0 + 1};
     }
-    constexpr size_t kSlack = 64 * 16;
-    const size_t field_bytes = (KICK && !BSPL && !WHOLE && known)
-                                   ? (size_t)fbox.h * fbox.w * sizeof(V) + kSlack
-                                   : 0;
+    constexpr size_t kSlack = 64 * kUnitBytes;
+    const size_t field_bytes =
+        (KICK && !WHOLE && known) ? (size_t)fbox.h * fbox.w * sizeof(S) + kSlack : 0;
     // LDS layout: [charge tile][staged field box and slack]
     Box tile{0, 0, 1, 1};
     size_t tile_bytes = 0;
@@ -759,8 +776,8 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
         tile_bytes = sizeof(uint32_t) * (size_t)tile.h * tile.w;
     }
     uint32_t *lq = reinterpret_cast<uint32_t *>(lds);
-    V *le = reinterpret_cast<V *>(lds + tile_bytes);
-    Box ebox{0, 0, 1, 1};
+    S *le = reinterpret_cast<S *>(lds + tile_bytes);
+    Box ebox{0, 0, kSpan, kSpan};
     bool staged = false;
     if constexpr (KICK) {
         staged = field_bytes && field_bytes + tile_bytes <= (size_t)lds_bytes;
@@ -770,7 +787,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
             // as much as fits, when that keeps at least half of its nodes
             // (the box's edges hold only the tails of the distribution; a
             // particle outside the staged part gathers from L2).
-            const int64_t room = (int64_t)(((size_t)lds_bytes - tile_bytes - kSlack) / sizeof(V));
+            const int64_t room = (int64_t)(((size_t)lds_bytes - tile_bytes - kSlack) / sizeof(S));
             if (2 * room >= (int64_t)fbox.h * fbox.w) {
                 int i0 = fbox.i0, i1 = fbox.i0 + fbox.h - 1, j0 = fbox.j0, j1 = fbox.j0 + fbox.w - 1;
                 while ((int64_t)(i1 - i0 + 1) * (j1 - j0 + 1) > room) {
@@ -783,7 +800,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
                         j1 -= kUnitNodes;
                     }
                 }
-                staged = i1 > i0 && j1 > j0;
+                staged = i1 - i0 >= kSpan && j1 - j0 >= kSpan;
                 if (staged) ebox = Box{i0, j0, i1 - i0 + 1, j1 - j0 + 1};
             }
         }
@@ -792,7 +809,8 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
             // l to slot l; lanes past the box repeat its last unit into the
             // slack): every load is in flight at once and none passes through
             // a register.
-            const V *ev = reinterpret_cast<const V *>(ef);
+            const S *ev = reinterpret_cast<const S *>(ef);
+            const int row = BSPL ? g.ny + 2 : g.ny;
             const int wu = ebox.w / kUnitNodes, units = ebox.h * wu;
             const float inv_w = 1.0f / (float)wu;
             const int lane = (int)threadIdx.x & (kWave - 1);
@@ -800,10 +818,13 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
                  t0 < units; t0 += (int)blockDim.x) {
                 const int t = min(t0 + lane, units - 1);
                 const int r = div_small(t, wu, inv_w);
-                const V *src = ev + (ebox.i0 + r) * g.ny + ebox.j0 + (t - r * wu) * kUnitNodes;
-                __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void *)(uintptr_t)src,
-                    (__attribute__((address_space(3))) void *)(le + t0 * kUnitNodes), 16, 0, 0);
+                const S *src = ev + (ebox.i0 + r) * row + ebox.j0 + (t - r * wu) * kUnitNodes;
+                auto *from = (const __attribute__((address_space(1))) void *)(uintptr_t)src;
+                auto *to = (__attribute__((address_space(3))) void *)(le + t0 * kUnitNodes);
+                if constexpr (kUnitBytes == 16)
+                    __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
+                else
+                    __builtin_amdgcn_global_load_lds(from, to, 4, 0, 0);
             }
         }
     }
@@ -858,15 +879,25 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
         LineCic lck;
         bool in = false;
         CellField<V> ev;
+        SplineNodes<TE> us;
         if constexpr (KICK) {
             in = act && cic(gc, cur.x, cur.y, ck) && (!LINE || line_cic(line, cur.sg, lck));
-            if constexpr (!BSPL) {
+            if constexpr (BSPL) {
+                if constexpr (!WHOLE) {
+                    const bool near = in && staged && ebox.template holds_cell<kSpan>(ck.i, ck.j);
+                    if (near) us.load(le + ebox.at(ck.i, ck.j), ebox.w);
+                    if (in && !near) {
+                        us.load(ef + ck.i * (g.ny + 2) + ck.j, g.ny + 2);
+                        wait_loads();
+                    }
+                }
+            } else {
                 const V *ge = reinterpret_cast<const V *>(ef);
                 const uint32_t row = (uint32_t)sizeof(V) * (uint32_t)g.ny;
                 if constexpr (WHOLE) {
                     if (in) ev.load(ge, (uint32_t)sizeof(V) * (uint32_t)(ck.i * g.ny + ck.j), row);
                 } else {
-                    const bool near = in && staged && ebox.holds_cell(ck.i, ck.j);
+                    const bool near = in && staged && ebox.template holds_cell<kSpan>(ck.i, ck.j);
                     if (near)
                         ev.load(le, (uint32_t)sizeof(V) * (uint32_t)ebox.at(ck.i, ck.j),
                                 (uint32_t)sizeof(V) * (uint32_t)ebox.w);
@@ -883,7 +914,8 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
             if (in) {
                 TE fx, fy;
                 if constexpr (BSPL) {
-                    bspline_field(g, ef, x, y, ck, fx, fy);
+                    if constexpr (WHOLE) us.load(ef + ck.i * (g.ny + 2) + ck.j, g.ny + 2);
+                    bspline_field(g, us, x, y, ck, fx, fy);
                 } else {
                     const Weights<TE> w(ck);
                     fx = w.sum(ev.e00.x, ev.e10.x, ev.e01.x, ev.e11.x);
@@ -1291,7 +1323,10 @@ hipError_t prepare_pass_kernels(size_t lds_per_workgroup)
 // one particle per lane, 27.5, 27.6 at two, 29.7, 28.7 at three, 31.7, 30.1 at
 // four.  The six-dimensional passes are bound by instruction issue and hide the
 // gathers: 28.1, 28.9 at four (1.04e6 particles), 68.5, 70.3 at eight, 106.3,
-// 108.9 at sixteen.
+// 108.9 at sixteen.  Under the B-spline gather (sixteen potentials per
+// particle) the lines lie no further apart: at four per lane, four-dimensional,
+// the staged box takes 33.9 us per step in FP64 (36.9 with the same pass
+// gathering from the L2) and 31.2 in the mixed form (31.1).
 bool whole_tile(const GridGeom &g, int64_t n, int nblk, int threads, bool six, size_t other_lds)
 {
     const int64_t most_per_lane = six ? 16 : 2;

@@ -783,12 +783,16 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
         staged = field_bytes && field_bytes + tile_bytes <= (size_t)lds_bytes;
         if (staged) ebox = fbox;
         if (field_bytes && !staged && tile_bytes + kSlack < (size_t)lds_bytes) {
-            // The whole box does not fit beside the tile: stage its centre,
-            // as much as fits, when that keeps at least half of its nodes
-            // (the box's edges hold only the tails of the distribution; a
-            // particle outside the staged part gathers from L2).
+            // The whole box does not fit beside the tile: stage its centre, as
+            // much as fits (the box's edges hold only the tails of the
+            // distribution; a particle outside the staged part gathers from
+            // L2).  From half of the nodes on; the streamed form, whose L2 and
+            // loads in order are the busier, from an eighth on.  Whole tracks
+            // with and without the centre, Gaussian beams in FP64: 8.8e6
+            // particles on 128^2 (streamed) 7.67 and 10.65 ms, 5e6 on 256^2
+            // (streamed) 6.64 and 6.67, 1.5e6 on 256^2 2.35 and 2.21.
             const int64_t room = (int64_t)(((size_t)lds_bytes - tile_bytes - kSlack) / sizeof(S));
-            if (2 * room >= (int64_t)fbox.h * fbox.w) {
+            if ((NT ? 8 : 2) * room >= (int64_t)fbox.h * fbox.w) {
                 int i0 = fbox.i0, i1 = fbox.i0 + fbox.h - 1, j0 = fbox.j0, j1 = fbox.j0 + fbox.w - 1;
                 while ((int64_t)(i1 - i0 + 1) * (j1 - j0 + 1) > room) {
                     // trim the longer side, one node (one unit) at each end

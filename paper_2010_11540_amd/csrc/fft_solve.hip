@@ -232,14 +232,17 @@ constexpr int kLineThreads = 256;   // batched column and row-inverse kernels
 // NT threads of the workgroup (NT >= ny).  Thread t reads 16-byte chunks (4 cells) of the row:
 // ny/4 lanes cover one workgroup's row segment and the NT/(ny/4) groups of
 // lanes split the workgroups.  Each lane reads the headers of its workgroups
-// itself (a group's lanes the same ones), then issues all of its chunk loads
+// itself (a group's lanes the same ones), then issues kReduceChunk chunk loads
 // before adding any: two rounds of memory latency for <= kReduceChunk
 // workgroups per lane, and no barrier between them.  Chunks outside a
 // workgroup's bounding box are not read (their loads return zeros without
 // touching memory).  red: LDS scratch of NT * 4 uint64; carry_v: this cell's
 // carry, loaded by the caller with its first round of loads (cleared here
 // when nonzero).  Returns the total of cell tid (tid < ny).
-constexpr int kReduceChunk = 8;
+// Four: most lanes have four workgroups or fewer (with eight the headers and
+// offsets of the missing ones are still worked through: 2414 us per small-ring
+// pass instead of 2365, 5807 per production pass instead of 5767).
+constexpr int kReduceChunk = 4;
 
 // Lane layout of a row reduction by NT threads: lanes = ny/4 16-byte chunks
 // cover one workgroup's row segment (ny is a multiple of 4), and groups =

@@ -123,8 +123,10 @@ def _check(code: int):
 
 
 def _stream_ptr(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if stream is None:
+        # the current stream's handle without a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return int(stream.cuda_stream)
 
 
 def _dev_f64(t: torch.Tensor, name: str) -> torch.Tensor:
@@ -137,12 +139,13 @@ def _dev_f64(t: torch.Tensor, name: str) -> torch.Tensor:
 def particles_struct(parts: dict) -> Particles:
     x = _dev_f64(parts["x"], "x")
     n = x.shape[0]
-    ptrs = []
-    for k in ("x", "px", "y", "py"):
+    dev = x.device
+    ptrs = [x.data_ptr()]
+    for k in ("px", "y", "py"):
         t = _dev_f64(parts[k], k)
         if t.shape[0] != n:
             raise ValueError(f"{k} has {t.shape[0]} entries, x has {n}")
-        if t.device != x.device:
+        if t.device != dev:
             raise ValueError("particle arrays must be on one device")
         ptrs.append(t.data_ptr())
     lost = parts.get("lost")
@@ -163,7 +166,7 @@ def particles_struct(parts: dict) -> Particles:
         t = parts.get(k)
         if t is not None:
             t = _dev_f64(t, k)
-            if t.shape[0] != n or t.device != x.device:
+            if t.shape[0] != n or t.device != dev:
                 raise ValueError(f"{k} must have n entries on the particles' device")
             t = t.data_ptr()
         longi.append(t)

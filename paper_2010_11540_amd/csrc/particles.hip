@@ -117,7 +117,7 @@ struct CellField {
     }
 };
 
-// Potential at the particle times 2^24 from its four nodes, as gather_nodes.
+// Potential at the particle times 2^24 from its four nodes, weighted as the field.
 template <typename TE>
 __device__ __forceinline__ TE gather_scalar(const TE *u, int l00, int row, const Cic &c)
 {

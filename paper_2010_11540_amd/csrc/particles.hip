@@ -877,7 +877,10 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
         const bool more = p0 + (NT ? 2 : 1) * T < P.n;
         const int64_t pn = more ? p0 + (NT ? 2 : 1) * T : p0, left = more ? P.n - pn : 1;
         Loaded next;
-        if constexpr (!WHOLE) next = load_particles<SIX, NT>(P, pn, left, weights);
+        // a push alone has one or two rounds and branches around the last one's:
+        // 1e6 particles 10.0 -> 9.2 us
+        if constexpr (!WHOLE)
+            if (KICK || DEPOSIT || more) next = load_particles<SIX, NT>(P, pn, left, weights);
         // the gathers
         Cic ck;
         LineCic lck;

@@ -590,6 +590,18 @@ __device__ __forceinline__ Loaded load_particles(const ParticlePtrs &P, int64_t 
     return v;
 }
 
+// Stores lane l's value at p[l], p the round's first particle (uniform): a store
+// to a buffer of `bytes` bytes, which an empty buffer (0) drops without a branch.
+template <bool NT>
+__device__ __forceinline__ void store_lane(double *p, uint32_t lane, double v, int bytes)
+{
+    using Words = uint32_t __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(
+        __builtin_bit_cast(Words, v),
+        __builtin_amdgcn_make_buffer_rsrc(p, (short)0, bytes, 0x00020000),
+        (int)(lane * sizeof(double)), 0, NT ? 2 : 0);  // 2: non-temporal
+}
+
 // Adds a particle's four weights to the workgroup's tile, where l is the tile
 // cell of node (i, j) and row the tile's row length.  A 32-bit cell wraps
 // after 2^32 units (256 particles on one node); the atomic's old value shows
@@ -627,7 +639,7 @@ __device__ __forceinline__ void deposit_cell(uint32_t *lq, int l, int row,
 // branch: a spare lane of a wave's last round repeats the last particle, which
 // is another lane's of the same wave (the same instructions load and store it
 // for both), but for its deposit, and a frozen particle stores its old
-// coordinates.
+// coordinates (unless its whole wave is frozen: the stores are then dropped).
 // For each particle:
 //   KICK     gather the node field at the particle with the deposit weights
 //            and kick px, py by kappa * w_p * E (w_p = 1 without weights);
@@ -994,28 +1006,30 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
                 }
             }
         }
-        if (moves) {
+        // A wave of frozen particles only stores nothing.  One with a moving particle
+        // stores all of its lanes' (whole lines; a frozen particle its old values):
+        // 8e6 particles on 128^2, one in two frozen at random, take 2.5 ms per 20
+        // steps, lane by lane they took 3.4.  The buffer's size makes the choice,
+        // not a branch, in front of which every wave would wait for its loads in
+        // flight (40 production steps, twice, mixed: 2.10 and 2.21 ms); a push
+        // alone, of few rounds, branches.  With all particles frozen, per 20
+        // steps: 1e6 on 128^2 0.45 -> 0.39 ms, 8e6 2.15 -> 1.15; a push of 8e6
+        // 97 -> 39 us.
+        const bool any = __any(act);
+        if (moves && (KICK || DEPOSIT || any)) {
             // the kick changes only the momenta; the elements move the
             // particle (a kick-only pass writes px and py alone)
             const bool shifts = FIRST != 0 || n_el > 0;
-            if constexpr (NT) {
-                if (shifts) {
-                    __builtin_nontemporal_store(x, P.x + p0 + lane);
-                    __builtin_nontemporal_store(y, P.y + p0 + lane);
-                }
-                __builtin_nontemporal_store(px, P.px + p0 + lane);
-                __builtin_nontemporal_store(py, P.py + p0 + lane);
-            } else {
-                if (shifts) {
-                    (P.x + p0)[lane] = x;
-                    (P.y + p0)[lane] = y;
-                }
-                (P.px + p0)[lane] = px;
-                (P.py + p0)[lane] = py;
+            const int bytes = any ? (int)(kWave * sizeof(double)) : 0;
+            if (shifts) {
+                store_lane<NT>(P.x + p0, lane, x, bytes);
+                store_lane<NT>(P.y + p0, lane, y, bytes);
             }
+            store_lane<NT>(P.px + p0, lane, px, bytes);
+            store_lane<NT>(P.py + p0, lane, py, bytes);
             if constexpr (SIX)
-                if (shifts) (P.sigma + p0)[lane] = sg;
-            if constexpr (LINE && KICK) (P.psigma + p0)[lane] = psg;
+                if (shifts) store_lane<false>(P.sigma + p0, lane, sg, bytes);
+            if constexpr (LINE && KICK) store_lane<false>(P.psigma + p0, lane, psg, bytes);
         }
         if constexpr (DEPOSIT) {
             cnt += __popcll(__ballot(hit));

@@ -671,7 +671,18 @@ __device__ __forceinline__ void deposit_cell(uint32_t *lq, int l, int row,
 // linear map (0: any elements).  The map's matrix then stays in registers for
 // the whole pass; read element by element inside the particle loop, its kind
 // and its parameters were two dependent scalar loads per element and round,
-// which nothing hid.
+// which nothing hid.  The streamed form takes no resident element (8e6
+// particles on 128^2, one 2x2 map a segment, FP64: 107 us with it, 101 without).
+//
+// The streamed form, bound by memory, does best when its waves keep step: each
+// waits for all its loads before it uses the field, also a wave that gathers
+// from LDS alone (with the wait left to the waves that gather from the L2, 5e6
+// particles on 128^2 took 71.2 us a pass instead of 65.5 in FP64, 72.3 and 64.3
+// mixed; the 1e7-particle KV beam on 256^2, mixed, is the exception, 124 and 128).
+// With the branches around its last loads and no resident element, whole tracks
+// of 20 steps: 5e6 on 128^2 1745 -> 1612 us FP64, 1750 -> 1572 mixed; 8e6 2456 ->
+// 2370; 1e7 on 256^2 5.74 -> 5.50 ms; the 64-beam scan, two turns, 6.17 -> 5.90 ms
+// FP64, 5.67 -> 5.51 mixed; the KV beam 2.82-2.96 -> 2.85-2.99 ms.
 //
 // MODE is a set of flags (0: four-dimensional).  1: the particles carry sigma
 // and p_sigma and els may hold thick elements; sigma is loaded and stored with
@@ -707,7 +718,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     constexpr bool WHOLE = (MODE & 16) != 0;
     static_assert(!WHOLE || DEPOSIT, "the tile is the depositing passes'");
     static_assert(!NT || !SIX, "the streamed pass is four-dimensional");
-    static_assert(!FIRST || !SIX, "a resident first element is four-dimensional");
+    static_assert(!FIRST || (!SIX && !NT), "a resident first element is four-dimensional, cached");
     extern __shared__ __align__(16) unsigned char lds_all[];
     // A pass that uses LDS reads its elements' parameters from there (one
     // broadcast read per value) but for a resident first element: read into
@@ -730,7 +741,6 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     double *const s_el = SIX ? s_el6 : reinterpret_cast<double *>(lds_all);
     constexpr bool PIN = !SIX && !BSPL;
     constexpr bool PIN_GRID = PIN && !NT && FIRST != SCPIC_EL_LIN4X4;
-    constexpr bool PIN_MAP = PIN && !(NT && FIRST == SCPIC_EL_LIN4X4);
     const GridCells gc = GridCells::of<PIN_GRID>(g);
     const int n_el = els.n_el;
     const int64_t T = (int64_t)nblk * blockDim.x;
@@ -866,7 +876,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     if constexpr (FIRST == SCPIC_EL_LIN2X2 || FIRST == SCPIC_EL_LIN4X4)
 #pragma unroll
         for (int k = 0; k < (FIRST == SCPIC_EL_LIN4X4 ? 16 : 8); ++k)
-            m0[k] = in_vector<PIN_MAP>(els.p[0][k]);
+            m0[k] = in_vector<PIN>(els.p[0][k]);
     wait_loads();  // the first round and the staged field
     if (KICK || DEPOSIT || SIX) __syncthreads();
 
@@ -889,10 +899,12 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
         const bool more = p0 + (NT ? 2 : 1) * T < P.n;
         const int64_t pn = more ? p0 + (NT ? 2 : 1) * T : p0, left = more ? P.n - pn : 1;
         Loaded next;
-        // a push alone has one or two rounds and branches around the last one's:
-        // 1e6 particles 10.0 -> 9.2 us
+        // a push alone has one or two rounds and branches around the last one's
+        // (1e6 particles 10.0 -> 9.2 us), and so does the streamed form (a
+        // deposit of 8e6 106 -> 96 us)
         if constexpr (!WHOLE)
-            if (KICK || DEPOSIT || more) next = load_particles<SIX, NT>(P, pn, left, weights);
+            if ((!NT && (KICK || DEPOSIT)) || more)
+                next = load_particles<SIX, NT>(P, pn, left, weights);
         // the gathers
         Cic ck;
         LineCic lck;
@@ -922,7 +934,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
                                 (uint32_t)sizeof(V) * (uint32_t)ebox.w);
                     if (in && !near) {
                         ev.load(ge, (uint32_t)sizeof(V) * (uint32_t)(ck.i * g.ny + ck.j), row);
-                        wait_loads();
+                        if constexpr (!NT) wait_loads();
                     }
                 }
             }
@@ -1091,7 +1103,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
 
 // FORM: 0, 8 (streamed, four-dimensional passes only) or 16 (the whole grid as
 // the tile, depositing passes only).  FIRST: the pass's first element, when it
-// is a linear map (four-dimensional passes only).
+// is a linear map (four-dimensional passes only, not streamed).
 template <typename TE, bool KICK, bool DEPOSIT, bool SIX, int FORM = 0, int FIRST = 0>
 __global__ void __launch_bounds__(1024)
     k_pass(ParticlePtrs P, GridGeom g, const TE *__restrict__ ef, double kappa,
@@ -1237,7 +1249,7 @@ hipError_t launch_pass_batched_t(hipStream_t s, const BatchLaunch &b, const Part
 }
 
 // Calls f with the integral constants of a pass's form and, for the passes of
-// a steady turn, of its resident first element.
+// a steady turn, of its resident first element (none in the streamed form).
 template <typename F>
 hipError_t with_form(bool whole, bool stream, F &&f)
 {
@@ -1245,11 +1257,13 @@ hipError_t with_form(bool whole, bool stream, F &&f)
     if (stream) return f(std::integral_constant<int, 8>{});
     return f(std::integral_constant<int, 0>{});
 }
-template <typename F>
+template <int FORM, typename F>
 hipError_t with_first(int first, F &&f)
 {
-    if (first == SCPIC_EL_LIN2X2) return f(std::integral_constant<int, SCPIC_EL_LIN2X2>{});
-    if (first == SCPIC_EL_LIN4X4) return f(std::integral_constant<int, SCPIC_EL_LIN4X4>{});
+    if constexpr (FORM != 8) {
+        if (first == SCPIC_EL_LIN2X2) return f(std::integral_constant<int, SCPIC_EL_LIN2X2>{});
+        if (first == SCPIC_EL_LIN4X4) return f(std::integral_constant<int, SCPIC_EL_LIN4X4>{});
+    }
     return f(std::integral_constant<int, 0>{});
 }
 
@@ -1257,8 +1271,10 @@ hipError_t with_first(int first, F &&f)
 template <typename TE, int FORM, int FIRST>
 void steady_kernels_of(std::vector<const void *> &out)
 {
-    out.push_back((const void *)k_pass<TE, true, true, false, FORM, FIRST>);
-    out.push_back((const void *)k_pass_batched<TE, true, true, false, FORM, FIRST>);
+    if constexpr (FORM != 8 || FIRST == 0) {
+        out.push_back((const void *)k_pass<TE, true, true, false, FORM, FIRST>);
+        out.push_back((const void *)k_pass_batched<TE, true, true, false, FORM, FIRST>);
+    }
     if constexpr (FORM != 8)
         out.push_back((const void *)k_pass_bspline<TE, true, true, false, FORM, FIRST>);
 }
@@ -1379,7 +1395,7 @@ hipError_t launch_pass_of(hipStream_t s, const ParticlePtrs &p, const GridGeom &
                 if (six)
                     return launch_pass_bspline_t<TE, true, true, true, FORM>(
                         s, p, g, phi, kappa, els, dep, blocks, threads);
-                return with_first(first_linear(els), [&](auto first) {
+                return with_first<FORM>(first_linear(els), [&](auto first) {
                     return launch_pass_bspline_t<TE, true, true, false, FORM,
                                                  decltype(first)::value>(s, p, g, phi, kappa, els,
                                                                          dep, blocks, threads);
@@ -1429,7 +1445,7 @@ hipError_t launch_pass_of(hipStream_t s, const ParticlePtrs &p, const GridGeom &
         if (!kick)
             return launch_pass_t<TE, false, true, false, FORM>(s, p, g, ef, kappa, els, dep, blocks,
                                                                threads);
-        return with_first(first_linear(els), [&](auto first) {
+        return with_first<FORM>(first_linear(els), [&](auto first) {
             return launch_pass_t<TE, true, true, false, FORM, decltype(first)::value>(
                 s, p, g, ef, kappa, els, dep, blocks, threads);
         });
@@ -1468,7 +1484,7 @@ hipError_t launch_pass_batched_of(hipStream_t s, const BatchLaunch &b, const Par
         if (!kick)
             return launch_pass_batched_t<TE, false, true, false, FORM>(s, b, all, steps, blocks,
                                                                        threads);
-        return with_first(f.first, [&](auto first) {
+        return with_first<FORM>(f.first, [&](auto first) {
             return launch_pass_batched_t<TE, true, true, false, FORM, decltype(first)::value>(
                 s, b, all, steps, blocks, threads);
         });

@@ -654,8 +654,8 @@ __device__ __forceinline__ void deposit_cell(uint32_t *lq, int l, int row,
 // Otherwise the tile covers the box the workgroup's
 // previous deposit recorded (its header; a workgroup owns the same particles
 // at every step of a track), and that box of the field (of the potential under
-// the B-spline gather), which holds every node the kick gathers from, is
-// staged in LDS beside the tile when it fits.
+// the four-dimensional B-spline gather), which holds every node the kick gathers
+// from, is staged in LDS beside the tile when it fits.
 // At the end each workgroup writes the bounding box of its tile cells to its
 // slice of the partials (no global atomics).
 //
@@ -778,8 +778,14 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
         fbox = Box{hd.i0, j0, hd.i1 + around - hd.i0 + 1, j1 - j0 + 1};
     }
     constexpr size_t kSlack = 64 * kUnitBytes;
+    // Not in the six-dimensional pass under the B-spline gather, which is bound by
+    // instruction issue and short of registers: staged or not, 1e6 particles on
+    // 100^2 take 905 us per 20 steps (FP64), and where only the box's centre fits
+    // the two ways to gather cost more than they save (256^2, 1e6: 1261 us staged,
+    // 1172 not; mixed 1187 and 1084; 2.5e6, FP64, 2175 and 1980).
+    constexpr bool STAGE = KICK && !WHOLE && !(SIX && BSPL);
     const size_t field_bytes =
-        (KICK && !WHOLE && known) ? (size_t)fbox.h * fbox.w * sizeof(S) + kSlack : 0;
+        (STAGE && known) ? (size_t)fbox.h * fbox.w * sizeof(S) + kSlack : 0;
     // LDS layout: [charge tile][staged field box and slack]
     Box tile{0, 0, 1, 1};
     size_t tile_bytes = 0;
@@ -915,12 +921,10 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
             in = act && cic(gc, cur.x, cur.y, ck) && (!LINE || line_cic(line, cur.sg, lck));
             if constexpr (BSPL) {
                 if constexpr (!WHOLE) {
-                    const bool near = in && staged && ebox.template holds_cell<kSpan>(ck.i, ck.j);
+                    const bool near =
+                        STAGE && in && staged && ebox.template holds_cell<kSpan>(ck.i, ck.j);
                     if (near) us.load(le + ebox.at(ck.i, ck.j), ebox.w);
-                    if (in && !near) {
-                        us.load(ef + ck.i * (g.ny + 2) + ck.j, g.ny + 2);
-                        wait_loads();
-                    }
+                    if (in && !near) us.load(ef + ck.i * (g.ny + 2) + ck.j, g.ny + 2);
                 }
             } else {
                 const V *ge = reinterpret_cast<const V *>(ef);

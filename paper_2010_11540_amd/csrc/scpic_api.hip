@@ -205,15 +205,13 @@ ParticlePtrs to_ptrs(const scpic_particles *p)
     return r;
 }
 
-// Threads per workgroup of a pass over n particles.  Automatic: 512 while no
-// workgroup then has a second round, so that a small beam spreads over more
-// compute units (FP64 us per step: 1e4 particles on 64^2 17.0 with 1024 threads,
-// 15.8 with 512, 16.1 with 256; 6.5e4 on 128^2 20.6, 19.8, 20.6; 1e5 21.1, 20.6,
-// 20.6); 1024 from there on, where waves count (1e6: 29.8, 31.5 with 512).
+// Threads per workgroup of a pass over n particles (every pass of n particles
+// the same, so that a workgroup keeps its particles from call to call).
 int threads_for(const scpic_ctx *c, int64_t n)
 {
     if (c->pass_threads > 0) return c->pass_threads;
-    return n <= (int64_t)512 * c->n_cu ? 512 : 1024;
+    const int limit = std::min(c->pass_blocks > 0 ? c->pass_blocks : c->n_cu, c->max_blocks);
+    return automatic_pass_threads(n, limit, c->n_cu);
 }
 
 // Workgroups of a pass over n particles.  A pass that kicks or deposits runs

@@ -82,6 +82,17 @@ struct PassElements {
     double p[kMaxPassElements][16];
 };
 
+// Threads per workgroup of a particle pass over n particles in at most `limit`
+// workgroups on n_cu compute units: 512 while no workgroup then has a second
+// round of particles, so that a small beam spreads over more compute units
+// (FP64 us per step: 1e4 particles on 64^2 17.0 with 1024 threads, 15.8 with
+// 512; 6.5e4 on 128^2 20.6 and 19.8), else 1024, where waves count (1e6 29.8,
+// 31.5 with 512; 6e4 particles in two workgroups 37.9, 48.0).
+inline int automatic_pass_threads(int64_t n, int limit, int n_cu)
+{
+    return n <= 512 * (int64_t)(limit < n_cu ? limit : n_cu) ? 512 : 1024;
+}
+
 // Device-side buffers of the charge partials.  Workgroup b of a depositing
 // pass writes the cells (i, j) of its bounding box to
 // partial[(i * max_blocks + b) * ny + j]: the partials of one grid row are

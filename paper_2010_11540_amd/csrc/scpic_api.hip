@@ -211,7 +211,7 @@ int threads_for(const scpic_ctx *c, int64_t n)
 {
     if (c->pass_threads > 0) return c->pass_threads;
     const int limit = std::min(c->pass_blocks > 0 ? c->pass_blocks : c->n_cu, c->max_blocks);
-    return automatic_pass_threads(n, limit, c->n_cu);
+    return automatic_pass_threads(n, (int64_t)c->geom.nx * c->geom.ny, limit, c->n_cu);
 }
 
 // Workgroups of a pass over n particles.  A pass that kicks or deposits runs

@@ -82,15 +82,21 @@ struct PassElements {
     double p[kMaxPassElements][16];
 };
 
-// Threads per workgroup of a particle pass over n particles in at most `limit`
-// workgroups on n_cu compute units: 512 while no workgroup then has a second
-// round of particles, so that a small beam spreads over more compute units
-// (FP64 us per step: 1e4 particles on 64^2 17.0 with 1024 threads, 15.8 with
-// 512; 6.5e4 on 128^2 20.6 and 19.8), else 1024, where waves count (1e6 29.8,
-// 31.5 with 512; 6e4 particles in two workgroups 37.9, 48.0).
-inline int automatic_pass_threads(int64_t n, int limit, int n_cu)
+// Threads per workgroup of a particle pass over n particles on a grid of
+// `cells` nodes, in at most `limit` workgroups on n_cu compute units: 512 while
+// no workgroup then has a second round of particles, so that a small beam
+// spreads over more compute units, else 1024, where waves count.  512 and 1024
+// threads, FP64, whole tracks of 32 steps relative to each other, mean of 2x2
+// maps, a KV beam, thick magnets and the B-spline field: 2e4 particles 0.93 on
+// 64^2, 0.95 on 128^2, 0.94 on 256^2; 5e4 0.94, 0.94, 1.01.  Twice the
+// workgroups also write and sum twice the partial grids, so beyond half as many
+// workgroups as compute units the grid counts: 1e5 particles 0.93 on 64^2, 0.99
+// on 100^2, 1.01 on 128^2, 1.03 on 200^2; 1.3e5 0.93, 1.00, 1.02, 1.07, and a
+// deposit alone on 256^2 19.7 us instead of 15.2.
+inline int automatic_pass_threads(int64_t n, int64_t cells, int limit, int n_cu)
 {
-    return n <= 512 * (int64_t)(limit < n_cu ? limit : n_cu) ? 512 : 1024;
+    const int64_t round = 512 * (int64_t)(limit < n_cu ? limit : n_cu);
+    return n <= (cells <= 10240 ? round : round / 2) ? 512 : 1024;
 }
 
 // Device-side buffers of the charge partials.  Workgroup b of a depositing

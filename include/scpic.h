@@ -257,9 +257,10 @@ scpic_status scpic_diagnose(scpic_ctx *ctx, const scpic_particles *parts, scpic_
  *                            per turn; 0: it launches the same kernels directly.
  *   SCPIC_OPT_PASS_BLOCKS    workgroups of the particle pass (0 = automatic:
  *                            one per compute unit).
- *   SCPIC_OPT_PASS_THREADS   threads per workgroup of the particle pass
- *                            (256, 512 or 1024; by default chosen from the
- *                            particle count).
+ *   SCPIC_OPT_PASS_THREADS   threads per workgroup of the particle pass (256,
+ *                            512 or 1024; 0 = automatic, the default: chosen
+ *                            from the particle count, the grid and
+ *                            SCPIC_OPT_PASS_BLOCKS).
  *   SCPIC_OPT_SOLVER         SCPIC_SOLVER_OPEN (default): the open-boundary
  *                            convolution of scpic_solve's comment;
  *                            SCPIC_SOLVER_PIPE (nx and ny powers of two, else

@@ -818,8 +818,8 @@ scpic_status scpic_set_option(scpic_ctx *ctx, int32_t option, int64_t value)
         return SCPIC_OK;
     }
     case SCPIC_OPT_PASS_THREADS:
-        if (value != 256 && value != 512 && value != 1024)
-            return fail(SCPIC_EINVAL, "pass threads must be 256, 512 or 1024");
+        if (value != 0 && value != 256 && value != 512 && value != 1024)
+            return fail(SCPIC_EINVAL, "pass threads must be 0 (automatic), 256, 512 or 1024");
         ctx->pass_threads = (int)value;
         return SCPIC_OK;
     default:

@@ -123,10 +123,13 @@ def _check(code: int):
 
 
 def _stream_ptr(stream) -> int:
-    if stream is None:
-        # the current stream's handle without a Stream object around it
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return int(stream.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # the current stream's handle without a Stream object around it, where torch gives it
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return raw(torch.cuda.current_device())
 
 
 def _dev_f64(t: torch.Tensor, name: str) -> torch.Tensor:

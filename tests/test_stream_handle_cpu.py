@@ -1,0 +1,20 @@
+"""The binding's stream handle: the given stream's, else the current one's, with and without torch's raw
+handle."""
+import types
+
+import torch
+
+from paper_2010_11540_amd import scpic
+
+
+def test_stream_handle(monkeypatch):
+    given = types.SimpleNamespace(cuda_stream=7)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=42))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device,
+                        raising=False)
+    assert scpic._stream_ptr(given) == 7
+    assert scpic._stream_ptr(None) == 103
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert scpic._stream_ptr(given) == 7
+    assert scpic._stream_ptr(None) == 42

@@ -35,24 +35,19 @@ struct Cic {
 // alive in its particle loop than scalar registers (the compiler then parks
 // them in lanes of a vector register and reads each back by an instruction of
 // its own), and vector registers to spare: one workgroup of 1024 threads has a
-// compute unit to itself, 128 registers per lane.  Not where a pass needs the
-// vector registers itself (PIN false: six dimensions, the B-spline field).
-template <bool PIN>
+// compute unit to itself, 128 registers per lane.
 __device__ __forceinline__ double in_vector(double v)
 {
-    if constexpr (PIN) asm("" : "+v"(v));
+    asm("" : "+v"(v));
     return v;
 }
 
 // The grid's geometry as cic() uses it.
 struct GridCells {
     double x_min, y_min, inv_dx, inv_dy, nx1, ny1;
-    template <bool PIN>
     static __device__ __forceinline__ GridCells of(const GridGeom &g)
     {
-        return {in_vector<PIN>(g.x_min),  in_vector<PIN>(g.y_min),
-                in_vector<PIN>(g.inv_dx), in_vector<PIN>(g.inv_dy),
-                in_vector<PIN>((double)(g.nx - 1)), in_vector<PIN>((double)(g.ny - 1))};
+        return {g.x_min, g.y_min, g.inv_dx, g.inv_dy, (double)(g.nx - 1), (double)(g.ny - 1)};
     }
 };
 
@@ -632,14 +627,18 @@ __device__ __forceinline__ void deposit_cell(uint32_t *lq, int l, int row,
 // walks its rounds of 64 particles from bid * blockDim.x + 64 w on in steps of
 // T = nblk * blockDim.x: consecutive lanes take consecutive particles, so
 // every SoA load and store is coalesced.  The loads of the next round (of the
-// one after next in the streamed form) are issued in each round: before the
-// gathers from LDS, after those from the L2 (memory operations complete in
-// order, and these would otherwise wait for memory instead of the cache).  For the
-// compiler to count on that order no common load or store stands behind a
-// branch: a spare lane of a wave's last round repeats the last particle, which
-// is another lane's of the same wave (the same instructions load and store it
-// for both), but for its deposit, and a frozen particle stores its old
-// coordinates (unless its whole wave is frozen: the stores are then dropped).
+// one after next in the streamed form) are issued in each round.  Memory
+// operations complete in order, so a gather from the L2 issued behind them waits
+// for memory: with the whole grid as the tile, where every lane gathers the field
+// from the L2, they come after it; in the other forms, where nearly every lane
+// gathers from LDS, before.  (Behind them all the same: the gathers of lanes
+// outside the staged box, the B-spline nodes of the whole-grid form, the line's
+// tables and potential.)  For the compiler to count on that order the cached forms
+// that kick or deposit have no common load or store behind a branch: a spare lane
+// of a wave's last round repeats the last particle, which is another lane's of the
+// same wave (the same instructions load and store it for both), but for its
+// deposit, and a frozen particle stores its old coordinates (unless its whole wave
+// is frozen: the stores are then dropped).
 // For each particle:
 //   KICK     gather the node field at the particle with the deposit weights
 //            and kick px, py by kappa * w_p * E (w_p = 1 without weights);
@@ -669,10 +668,11 @@ __device__ __forceinline__ void deposit_cell(uint32_t *lq, int l, int row,
 //
 // FIRST: the kind of the pass's first element when the caller knows it to be a
 // linear map (0: any elements).  The map's matrix then stays in registers for
-// the whole pass; read element by element inside the particle loop, its kind
-// and its parameters were two dependent scalar loads per element and round,
-// which nothing hid.  The streamed form takes no resident element (8e6
-// particles on 128^2, one 2x2 map a segment, FP64: 107 us with it, 101 without).
+// the whole pass; read inside the particle loop, its kind and its parameters were
+// two dependent scalar loads per round, which nothing hid (a later element's
+// parameters come from LDS, its kind from a scalar load).  The streamed form
+// takes no resident element (8e6 particles on 128^2, one 2x2 map a segment, FP64:
+// 107 us with it, 101 without).
 //
 // The streamed form, bound by memory, does best when its waves keep step: each
 // waits for all its loads before it uses the field, also a wave that gathers
@@ -739,9 +739,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     __shared__ double s_el6[SIX ? kMaxPassElements * 16 : 1];
     static_assert(sizeof(s_el6) + 256 <= kPassStaticLds, "static LDS beyond the reserved share");
     double *const s_el = SIX ? s_el6 : reinterpret_cast<double *>(lds_all);
-    constexpr bool PIN = !SIX && !BSPL;
-    constexpr bool PIN_GRID = PIN && !NT && FIRST != SCPIC_EL_LIN4X4;
-    const GridCells gc = GridCells::of<PIN_GRID>(g);
+    const GridCells gc = GridCells::of(g);
     const int n_el = els.n_el;
     const int64_t T = (int64_t)nblk * blockDim.x;
     int64_t p0 = (int64_t)bid * blockDim.x +
@@ -877,12 +875,15 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     if (SIX || el_bytes)
         for (int t = threadIdx.x; t < n_el * 16; t += blockDim.x)
             s_el[t] = els.p[t >> 4][t & 15];
-    // the resident first element
+    // the resident first element, in vector registers but under the B-spline
+    // gather, which needs them for its nodes (40 production steps, twice: 2.25 ms,
+    // in scalar registers 2.27, mixed 2.11 and 2.15; with the B-spline field, 25
+    // steps twice, 1.76 and 1.58, mixed 1.44 and 1.48)
     double m0[16] = {};
     if constexpr (FIRST == SCPIC_EL_LIN2X2 || FIRST == SCPIC_EL_LIN4X4)
 #pragma unroll
         for (int k = 0; k < (FIRST == SCPIC_EL_LIN4X4 ? 16 : 8); ++k)
-            m0[k] = in_vector<PIN>(els.p[0][k]);
+            m0[k] = BSPL ? els.p[0][k] : in_vector(els.p[0][k]);
     wait_loads();  // the first round and the staged field
     if (KICK || DEPOSIT || SIX) __syncthreads();
 
@@ -1359,14 +1360,21 @@ hipError_t prepare_pass_kernels(size_t lds_per_workgroup)
 // Whether a depositing pass takes the whole grid as its tile: when it fits in
 // LDS and each of the nblk * threads lanes has few particles.  The other form's
 // set-up (the header's read, then the field box moved into LDS) is about 1 us
-// and its gathers then take no part in the L2's traffic.  Four-dimensional
-// passes on 128^2, FP64, us per step, whole grid and staged box: 24.0, 24.6 at
-// one particle per lane, 27.5, 27.6 at two, 29.7, 28.7 at three, 31.7, 30.1 at
-// four.  The six-dimensional passes are bound by instruction issue and hide the
-// gathers: 28.1, 28.9 at four (1.04e6 particles), 68.5, 70.3 at eight, 106.3,
-// 108.9 at sixteen.  Under the B-spline gather (sixteen potentials per
-// particle) the lines lie no further apart: at four per lane, four-dimensional,
-// the staged box takes 33.9 us per step in FP64 (36.9 with the same pass
+// and its gathers then take no part in the L2's traffic.
+// Four dimensions, tracks of 32 steps, FP64, us whole and staged at 1, 2, 3 and 4
+// particles per lane: a Gaussian beam on 128^2 692, 712; 804, 799; 874, 819; 953,
+// 873; on 200^2, where its box does not fit, 1015, 1116; 1107, 1164; 1181, 1207;
+// 1277, 1309; a KV beam, whose box always fits, on 128^2 637, 652; 731, 719; 827,
+// 775; 940, 880; on 200^2 909, 897; 1012, 955; 1111, 988; 1225, 1074.  The size
+// alone does not say whether the box will fit, so the line at two is between the
+// two beams'.
+// The six-dimensional passes are bound by instruction issue and hide the gathers:
+// the thick ring, 10 steps, at 8, 16, 24 and 32 per lane on 128^2 666, 683; 1155,
+// 1188; 1937, 1688; 2360, 2209; on 200^2 750, 775; 1255, 1298; 2230, 2196; 2874,
+// 2806; with the line density 772, 768 at 8, 1277, 1250 at 16 and 3275, 2784 at 32;
+// under the B-spline gather the two forms, neither of which stages its box, are
+// within 1 % from 8 to 32.  Four dimensions under the B-spline gather, four per
+// lane: the staged box takes 33.9 us per step in FP64 (36.9 with the same pass
 // gathering from the L2) and 31.2 in the mixed form (31.1).
 bool whole_tile(const GridGeom &g, int64_t n, int nblk, int threads, bool six, size_t other_lds)
 {

@@ -24,8 +24,10 @@
 //                by Hermitian symmetry, one inverse FFT     -> ex, ey [nx][ny]
 // Taking the differences in the spectrum keeps the large constant part of
 // the potential out of the field's rounding, which matters for the FP32 form.
-// Every kernel issues all of its global loads into registers before its
-// first transform, so each kernel waits for one round of memory latency.
+// The column and row-inverse kernels issue all of their global loads into
+// registers before their first transform and so wait for one round of memory
+// latency; the row kernel for two per kReduceChunk partial slices of a lane (the
+// headers, then the slices).
 #include <algorithm>
 #include <type_traits>
 
@@ -233,15 +235,17 @@ constexpr int kLineThreads = 256;   // batched column and row-inverse kernels
 // ny/4 lanes cover one workgroup's row segment and the NT/(ny/4) groups of
 // lanes split the workgroups.  Each lane reads the headers of its workgroups
 // itself (a group's lanes the same ones), then issues kReduceChunk chunk loads
-// before adding any: two rounds of memory latency for <= kReduceChunk
-// workgroups per lane, and no barrier between them.  Chunks outside a
+// before adding any: two rounds of memory latency for kReduceChunk workgroups
+// per lane, and no barrier between them.  Chunks outside a
 // workgroup's bounding box are not read (their loads return zeros without
 // touching memory).  red: LDS scratch of NT * 4 uint64; carry_v: this cell's
 // carry, loaded by the caller with its first round of loads (cleared here
 // when nonzero).  Returns the total of cell tid (tid < ny).
-// Four: most lanes have four workgroups or fewer (with eight the headers and
-// offsets of the missing ones are still worked through: 2414 us per small-ring
-// pass instead of 2365, 5807 per production pass instead of 5767).
+// Four at a time is the faster also where a lane has more workgroups (with 256
+// pass workgroups 4 at ny = 64, 8 at 128, 16 at 256) and so twice the rounds.
+// Row kernel, us, four and eight: 1e4 particles on 64^2 4.4, 5.0; 1e6 on 64^2 4.9,
+// 5.8; on 128^2 6.4, 6.6; on 176^2 7.7, 8.8; on 256^2 10.0, 11.0.  Eight only where
+// a lane has more than four: 6.6 on 128^2, 8.7 on 176^2, 10.9 on 256^2.
 constexpr int kReduceChunk = 4;
 
 // Lane layout of a row reduction by NT threads: lanes = ny/4 16-byte chunks

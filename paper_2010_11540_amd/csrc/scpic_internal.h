@@ -58,13 +58,14 @@ struct GridGeom {
 // i = floor(t), a = floor((t - i) 4096 + 0.5), each operation rounded to
 // nearest, evaluated as one conversion: 8192 t, exact, truncated to an integer
 // v = 8192 i + floor(8192 (t - i)), and a = floor((floor(2 u) + 1) / 2) =
-// floor(u + 0.5) for u = 4096 (t - i).  The two agree wherever u + 0.5 is
-// exact in 53 bits, which it is for u >= 0.5 (the sum's last place is not
-// above u's) and, below 0.5, for every u but 0.5 - 2^-54: there the rounded
-// sum is 1, so a = 1.  Adding 2^-54 to 8192 t gives that one value (a tie,
-// 1 - 2^-53 -> 1) and leaves every other in its integer interval: it is under
-// half a unit of the last place from 2^-1 on but for the tie, and cannot reach
-// 1 from below 2^-1.  16 FP64 and conversion operations become 4.
+// floor(u + 0.5) for u = 4096 (t - i).  The rounded sum u + 0.5 has the same
+// floor unless rounding lifts it to an integer k.  For k > 1 no power of two lies
+// between u = k - 0.5 and k, so that the sum's last place is u's and the sum is
+// exact; just below k = 1 it is not, and one value is lifted: 0.5 - 2^-54, whose
+// sum, a tie, rounds to 1.  Adding 2^-54 to 8192 t gives that one value (a tie,
+// 1 - 2^-53 -> 1) and leaves every other in its integer interval: it is at most
+// half a unit of the last place from 2^-1 on, and cannot reach 1 from below 2^-1.
+// 16 FP64 and conversion operations become 4.
 __host__ __device__ inline void cell_fraction(double t, int &i, int &a)
 {
     const int v = (int)__builtin_fma(t, 8192.0, 0x1p-54);
@@ -165,7 +166,7 @@ inline int stage_twiddle_exponent(int e, int L, int log2L)
 // is read from, or -1 for an entry that is zero: the zero-padded column (open
 // boundary), or its odd extension about the walls at k = 0 and k = nx
 // (grounded pipe, mx = 2 nx; entries k > nx take the row's negative).  Any
-// k >= 0 is accepted: the lanes of a kernel beyond mx read nothing.
+// k >= 0 is accepted (k >= mx: zero); the column kernels' lanes cover k < mx.
 __host__ __device__ constexpr int column_source(int k, int nx, int mx, bool pipe)
 {
     if (k >= mx) return -1;
@@ -251,8 +252,9 @@ hipError_t prepare_pass_kernels(size_t lds_per_workgroup);
 // True when els holds a thick element (the pass then needs sigma, p_sigma).
 bool has_thick(const PassElements &els);
 
-// The kind of els' first element when that is a linear map, else 0 (the passes
-// that kick and deposit then keep its matrix in scalar registers).
+// The kind of els' first element when that is a linear map, else 0 (the cached
+// four-dimensional passes that kick and deposit then keep its matrix in
+// registers).
 int first_linear(const PassElements &els);
 
 // Whether a depositing pass of nblk workgroups over n particles takes the

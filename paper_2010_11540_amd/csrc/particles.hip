@@ -556,8 +556,11 @@ __device__ __forceinline__ uint32_t round_lane(int64_t left)
 // offset.  Every lane loads (round_lane), and the flags and weights are not
 // looked at here, which would wait for the loads.  Without a
 // lost array the flag loads some byte that the caller ignores, so that the
-// number of loads in flight does not depend on a branch.
-template <bool SIX, bool NT>
+// number of loads in flight does not depend on a branch; FLAG_BRANCH: it branches
+// (the streamed passes that kick or deposit, whose waves wait for all their loads
+// anyway: without a lost array a deposit of 6e6 40.4 -> 39.7 us, with one tracks of
+// 8e6 on 128^2 2.37 -> 2.29 ms per 20 steps; a push alone 71.3 -> 73.7).
+template <bool SIX, bool NT, bool FLAG_BRANCH = false>
 __device__ __forceinline__ Loaded load_particles(const ParticlePtrs &P, int64_t p0, int64_t left,
                                                  bool weights)
 {
@@ -581,7 +584,8 @@ __device__ __forceinline__ Loaded load_particles(const ParticlePtrs &P, int64_t 
         v.sg = (P.sigma + p0)[lane];
         v.psg = (P.psigma + p0)[lane];
     }
-    v.lost = lost[lane];
+    v.lost = 0;
+    if (!FLAG_BRANCH || P.lost) v.lost = lost[lane];
     return v;
 }
 
@@ -896,8 +900,8 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     // (its loads come from memory, not the last-level cache).
     Loaded ahead;
     if (NT && p0 < P.n)
-        ahead = load_particles<SIX, true>(P, p0 + T < P.n ? p0 + T : p0,
-                                          p0 + T < P.n ? P.n - p0 - T : 1, weights);
+        ahead = load_particles<SIX, true, KICK || DEPOSIT>(
+            P, p0 + T < P.n ? p0 + T : p0, p0 + T < P.n ? P.n - p0 - T : 1, weights);
     const bool has_lost = P.lost != nullptr;
     for (; p0 < P.n; p0 += T) {
         const uint32_t lane = round_lane(P.n - p0);
@@ -911,7 +915,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
         // deposit of 8e6 106 -> 96 us)
         if constexpr (!WHOLE)
             if ((!NT && (KICK || DEPOSIT)) || more)
-                next = load_particles<SIX, NT>(P, pn, left, weights);
+                next = load_particles<SIX, NT, NT && (KICK || DEPOSIT)>(P, pn, left, weights);
         // the gathers
         Cic ck;
         LineCic lck;

@@ -122,14 +122,16 @@ def _check(code: int):
         raise ScpicError(code, load_library().scpic_last_error().decode())
 
 
+# the current stream's handle without a Stream object around it, where torch gives it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream) -> int:
     if stream is not None:
         return int(stream.cuda_stream)
-    # the current stream's handle without a Stream object around it, where torch gives it
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if raw is None:
+    if _raw_stream is None:
         return int(torch.cuda.current_stream().cuda_stream)
-    return raw(torch.cuda.current_device())
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev_f64(t: torch.Tensor, name: str) -> torch.Tensor:

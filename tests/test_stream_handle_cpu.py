@@ -11,10 +11,9 @@ def test_stream_handle(monkeypatch):
     given = types.SimpleNamespace(cuda_stream=7)
     monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=42))
-    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device,
-                        raising=False)
+    monkeypatch.setattr(scpic, "_raw_stream", lambda device: 100 + device)
     assert scpic._stream_ptr(given) == 7
     assert scpic._stream_ptr(None) == 103
-    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    monkeypatch.setattr(scpic, "_raw_stream", None)
     assert scpic._stream_ptr(given) == 7
     assert scpic._stream_ptr(None) == 42

@@ -557,9 +557,9 @@ __device__ __forceinline__ uint32_t round_lane(int64_t left)
 // looked at here, which would wait for the loads.  Without a
 // lost array the flag loads some byte that the caller ignores, so that the
 // number of loads in flight does not depend on a branch; FLAG_BRANCH: it branches
-// (the streamed passes that kick or deposit, whose waves wait for all their loads
-// anyway: without a lost array a deposit of 6e6 40.4 -> 39.7 us, with one tracks of
-// 8e6 on 128^2 2.37 -> 2.29 ms per 20 steps; a push alone 71.3 -> 73.7).
+// (the passes in step, which wait for all their loads anyway: without a lost array
+// a deposit of 6e6 40.4 -> 39.7 us, with one tracks of 8e6 on 128^2 2.37 -> 2.29 ms
+// per 20 steps; a push alone 71.3 -> 73.7).
 template <bool SIX, bool NT, bool FLAG_BRANCH = false>
 __device__ __forceinline__ Loaded load_particles(const ParticlePtrs &P, int64_t p0, int64_t left,
                                                  bool weights)
@@ -674,19 +674,20 @@ __device__ __forceinline__ void deposit_cell(uint32_t *lq, int l, int row,
 // linear map (0: any elements).  The map's matrix then stays in registers for
 // the whole pass; read inside the particle loop, its kind and its parameters were
 // two dependent scalar loads per round, which nothing hid (a later element's
-// parameters come from LDS, its kind from a scalar load).  The streamed form
-// takes no resident element (8e6 particles on 128^2, one 2x2 map a segment, FP64:
-// 107 us with it, 101 without).
+// parameters come from LDS, its kind from a scalar load).
 //
-// The streamed form, bound by memory, does best when its waves keep step: each
-// waits for all its loads before it uses the field, also a wave that gathers
-// from LDS alone (with the wait left to the waves that gather from the L2, 5e6
-// particles on 128^2 took 71.2 us a pass instead of 65.5 in FP64, 72.3 and 64.3
-// mixed; the 1e7-particle KV beam on 256^2, mixed, is the exception, 124 and 128).
-// With the branches around its last loads and no resident element, whole tracks
-// of 20 steps: 5e6 on 128^2 1745 -> 1612 us FP64, 1750 -> 1572 mixed; 8e6 2456 ->
-// 2370; 1e7 on 256^2 5.74 -> 5.50 ms; the 64-beam scan, two turns, 6.17 -> 5.90 ms
-// FP64, 5.67 -> 5.51 mixed; the KV beam 2.82-2.96 -> 2.85-2.99 ms.
+// The streamed form is bound by memory.  With workgroups of 1024 threads it does
+// best in step (STEP): each wave waits for all its loads before it uses the field,
+// also one that gathers from LDS alone, branches around the loads of its last
+// rounds and keeps no element in registers.  5e6 particles on 128^2, us a pass:
+// 71.2 with the wait left to the waves that gather from the L2, 65.5 in step
+// (FP64), 72.3 and 64.3 (mixed); 8e6, one 2x2 map a segment, 107 with the map in
+// registers, 101 without.  Whole tracks of 20 steps: 5e6 on 128^2 1740 -> 1600 us
+// FP64, 1760 -> 1560 mixed; 8e6 2465 -> 2290; 1e7 on 256^2 5.73 -> 5.46 ms; the
+// 64-beam scan, two turns, 6.21 -> 5.85 ms FP64, 5.67 -> 5.44 mixed; the KV beam of
+// 1e7 on 256^2, mixed, 2.93 -> 2.83-2.94.  With fewer threads, which have to hide
+// the latency themselves, it is the ordered form: 5e6 with 512 threads 2.00 ms in
+// step, 1.53 ordered, with 256 2.98 and 1.99.
 //
 // MODE is a set of flags (0: four-dimensional).  1: the particles carry sigma
 // and p_sigma and els may hold thick elements; sigma is loaded and stored with
@@ -704,6 +705,7 @@ __device__ __forceinline__ void deposit_cell(uint32_t *lq, int l, int row,
 // 8: the four transverse coordinates are streamed with non-temporal loads and
 // stores (particle arrays far larger than the last-level cache, which they
 // would only churn; smaller ones stay cached between passes).  16: WHOLE.
+// 32: STEP.
 // The body is shared by the single-beam kernel and the batched one: bid is
 // the workgroup's index among the nblk workgroups working on beam P (its
 // slice of the partials and its header).
@@ -720,9 +722,11 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     constexpr bool BSPL = (MODE & 4) != 0;
     constexpr bool NT = (MODE & 8) != 0;
     constexpr bool WHOLE = (MODE & 16) != 0;
+    constexpr bool STEP = (MODE & 32) != 0;
     static_assert(!WHOLE || DEPOSIT, "the tile is the depositing passes'");
     static_assert(!NT || !SIX, "the streamed pass is four-dimensional");
-    static_assert(!FIRST || (!SIX && !NT), "a resident first element is four-dimensional, cached");
+    static_assert(!STEP || (NT && (KICK || DEPOSIT)), "in step: streamed passes that use LDS");
+    static_assert(!FIRST || (!SIX && !STEP), "a resident first element is four-dimensional");
     extern __shared__ __align__(16) unsigned char lds_all[];
     // A pass that uses LDS reads its elements' parameters from there (one
     // broadcast read per value) but for a resident first element: read into
@@ -879,15 +883,16 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     if (SIX || el_bytes)
         for (int t = threadIdx.x; t < n_el * 16; t += blockDim.x)
             s_el[t] = els.p[t >> 4][t & 15];
-    // the resident first element, in vector registers but under the B-spline
-    // gather, which needs them for its nodes (40 production steps, twice: 2.25 ms,
-    // in scalar registers 2.27, mixed 2.11 and 2.15; with the B-spline field, 25
-    // steps twice, 1.76 and 1.58, mixed 1.44 and 1.48)
+    // the resident first element, in vector registers (40 production steps, twice:
+    // 2.25 ms, in scalar registers 2.27, mixed 2.11 and 2.15) but under the B-spline
+    // gather, which needs them for its nodes (25 steps twice, 1.76 and 1.58 ms,
+    // mixed 1.44 and 1.48), and for a streamed 4x4 map, where they do not suffice
+    // (40 bytes of scratch per lane, 5e6 particles on 128^2 87 us a pass and 71)
     double m0[16] = {};
     if constexpr (FIRST == SCPIC_EL_LIN2X2 || FIRST == SCPIC_EL_LIN4X4)
 #pragma unroll
         for (int k = 0; k < (FIRST == SCPIC_EL_LIN4X4 ? 16 : 8); ++k)
-            m0[k] = BSPL ? els.p[0][k] : in_vector(els.p[0][k]);
+            m0[k] = BSPL || (NT && FIRST == SCPIC_EL_LIN4X4) ? els.p[0][k] : in_vector(els.p[0][k]);
     wait_loads();  // the first round and the staged field
     if (KICK || DEPOSIT || SIX) __syncthreads();
 
@@ -900,7 +905,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     // (its loads come from memory, not the last-level cache).
     Loaded ahead;
     if (NT && p0 < P.n)
-        ahead = load_particles<SIX, true, KICK || DEPOSIT>(
+        ahead = load_particles<SIX, true, STEP>(
             P, p0 + T < P.n ? p0 + T : p0, p0 + T < P.n ? P.n - p0 - T : 1, weights);
     const bool has_lost = P.lost != nullptr;
     for (; p0 < P.n; p0 += T) {
@@ -911,11 +916,11 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
         const int64_t pn = more ? p0 + (NT ? 2 : 1) * T : p0, left = more ? P.n - pn : 1;
         Loaded next;
         // a push alone has one or two rounds and branches around the last one's
-        // (1e6 particles 10.0 -> 9.2 us), and so does the streamed form (a
+        // (1e6 particles 10.0 -> 9.2 us), and so does the form in step (a
         // deposit of 8e6 106 -> 96 us)
         if constexpr (!WHOLE)
-            if ((!NT && (KICK || DEPOSIT)) || more)
-                next = load_particles<SIX, NT, NT && (KICK || DEPOSIT)>(P, pn, left, weights);
+            if ((!STEP && (KICK || DEPOSIT)) || more)
+                next = load_particles<SIX, NT, STEP>(P, pn, left, weights);
         // the gathers
         Cic ck;
         LineCic lck;
@@ -943,7 +948,7 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
                                 (uint32_t)sizeof(V) * (uint32_t)ebox.w);
                     if (in && !near) {
                         ev.load(ge, (uint32_t)sizeof(V) * (uint32_t)(ck.i * g.ny + ck.j), row);
-                        if constexpr (!NT) wait_loads();
+                        if constexpr (!STEP) wait_loads();
                     }
                 }
             }
@@ -1110,9 +1115,10 @@ __device__ __forceinline__ void pass_body(const ParticlePtrs &P, const GridGeom 
     }
 }
 
-// FORM: 0, 8 (streamed, four-dimensional passes only) or 16 (the whole grid as
-// the tile, depositing passes only).  FIRST: the pass's first element, when it
-// is a linear map (four-dimensional passes only, not streamed).
+// FORM: 0, 8 (streamed, four-dimensional passes only), 40 (streamed and in step)
+// or 16 (the whole grid as the tile, depositing passes only).  FIRST: the pass's
+// first element, when it is a linear map (four-dimensional passes only, not in
+// step).
 template <typename TE, bool KICK, bool DEPOSIT, bool SIX, int FORM = 0, int FIRST = 0>
 __global__ void __launch_bounds__(1024)
     k_pass(ParticlePtrs P, GridGeom g, const TE *__restrict__ ef, double kappa,
@@ -1258,18 +1264,19 @@ hipError_t launch_pass_batched_t(hipStream_t s, const BatchLaunch &b, const Part
 }
 
 // Calls f with the integral constants of a pass's form and, for the passes of
-// a steady turn, of its resident first element (none in the streamed form).
+// a steady turn, of its resident first element (none in step).
 template <typename F>
-hipError_t with_form(bool whole, bool stream, F &&f)
+hipError_t with_form(bool whole, bool stream, int threads, F &&f)
 {
     if (whole) return f(std::integral_constant<int, 16>{});
+    if (stream && threads >= 1024) return f(std::integral_constant<int, 40>{});
     if (stream) return f(std::integral_constant<int, 8>{});
     return f(std::integral_constant<int, 0>{});
 }
 template <int FORM, typename F>
 hipError_t with_first(int first, F &&f)
 {
-    if constexpr (FORM != 8) {
+    if constexpr (FORM != 40) {
         if (first == SCPIC_EL_LIN2X2) return f(std::integral_constant<int, SCPIC_EL_LIN2X2>{});
         if (first == SCPIC_EL_LIN4X4) return f(std::integral_constant<int, SCPIC_EL_LIN4X4>{});
     }
@@ -1280,11 +1287,11 @@ hipError_t with_first(int first, F &&f)
 template <typename TE, int FORM, int FIRST>
 void steady_kernels_of(std::vector<const void *> &out)
 {
-    if constexpr (FORM != 8 || FIRST == 0) {
+    if constexpr (FORM != 40 || FIRST == 0) {
         out.push_back((const void *)k_pass<TE, true, true, false, FORM, FIRST>);
         out.push_back((const void *)k_pass_batched<TE, true, true, false, FORM, FIRST>);
     }
-    if constexpr (FORM != 8)
+    if constexpr (!(FORM & 8))
         out.push_back((const void *)k_pass_bspline<TE, true, true, false, FORM, FIRST>);
 }
 template <typename TE, int FORM>
@@ -1299,7 +1306,7 @@ void form_kernels_of(std::vector<const void *> &four, std::vector<const void *> 
         four.push_back((const void *)k_pass<TE, true, false, false, FORM>);
         four.push_back((const void *)k_pass_batched<TE, true, false, false, FORM>);
     }
-    if constexpr (FORM != 8) {
+    if constexpr (!(FORM & 8)) {
         six.push_back((const void *)k_pass<TE, true, true, true, FORM>);
         six.push_back((const void *)k_pass<TE, false, true, true, FORM>);
         six.push_back((const void *)k_pass_batched<TE, true, true, true, FORM>);
@@ -1345,9 +1352,11 @@ hipError_t prepare_pass_kernels(size_t lds_per_workgroup)
     form_kernels_of<double, 0>(four, six);
     form_kernels_of<double, 8>(four, six);
     form_kernels_of<double, 16>(four, six);
+    form_kernels_of<double, 40>(four, six);
     form_kernels_of<float, 0>(four, six);
     form_kernels_of<float, 8>(four, six);
     form_kernels_of<float, 16>(four, six);
+    form_kernels_of<float, 40>(four, six);
     for (const void *k : four) {
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)g_lds_limit);
@@ -1405,9 +1414,9 @@ hipError_t launch_pass_of(hipStream_t s, const ParticlePtrs &p, const GridGeom &
                                                                       blocks, threads)
                        : launch_pass_bspline_t<TE, true, false, false>(s, p, g, phi, kappa, els,
                                                                        dep, blocks, threads);
-        return with_form(whole, false, [&](auto form) {
+        return with_form(whole, false, threads, [&](auto form) {
             constexpr int FORM = decltype(form)::value;
-            if constexpr (FORM != 8) {
+            if constexpr (!(FORM & 8)) {
                 if (six)
                     return launch_pass_bspline_t<TE, true, true, true, FORM>(
                         s, p, g, phi, kappa, els, dep, blocks, threads);
@@ -1424,9 +1433,9 @@ hipError_t launch_pass_of(hipStream_t s, const ParticlePtrs &p, const GridGeom &
         if (!deposit)
             return launch_pass_line_t<TE, true, false>(s, p, g, ef, kappa, els, dep, blocks,
                                                        threads, *line);
-        return with_form(whole, false, [&](auto form) {
+        return with_form(whole, false, threads, [&](auto form) {
             constexpr int FORM = decltype(form)::value;
-            if constexpr (FORM != 8)
+            if constexpr (!(FORM & 8))
                 return kick ? launch_pass_line_t<TE, true, true, FORM>(s, p, g, ef, kappa, els, dep,
                                                                        blocks, threads, *line)
                             : launch_pass_line_t<TE, false, true, FORM>(
@@ -1440,19 +1449,19 @@ hipError_t launch_pass_of(hipStream_t s, const ParticlePtrs &p, const GridGeom &
                                                                threads)
                         : launch_pass_t<TE, false, false, true>(s, p, g, ef, kappa, els, dep,
                                                                 blocks, threads);
-        return with_form(false, p.stream, [&](auto form) {
+        return with_form(false, p.stream, threads, [&](auto form) {
             constexpr int FORM = decltype(form)::value;
             if constexpr (FORM != 16)
                 return kick ? launch_pass_t<TE, true, false, false, FORM>(s, p, g, ef, kappa, els,
                                                                           dep, blocks, threads)
-                            : launch_pass_t<TE, false, false, false, FORM>(
+                            : launch_pass_t<TE, false, false, false, FORM & 31>(
                                   s, p, g, ef, kappa, els, dep, blocks, threads);
             return hipErrorInvalidValue;
         });
     }
-    return with_form(whole, p.stream && !six, [&](auto form) {
+    return with_form(whole, p.stream && !six, threads, [&](auto form) {
         constexpr int FORM = decltype(form)::value;
-        if constexpr (FORM != 8)
+        if constexpr (!(FORM & 8))
             if (six)
                 return kick ? launch_pass_t<TE, true, true, true, FORM>(s, p, g, ef, kappa, els,
                                                                         dep, blocks, threads)
@@ -1479,19 +1488,19 @@ hipError_t launch_pass_batched_of(hipStream_t s, const BatchLaunch &b, const Par
                                                                        threads)
                         : launch_pass_batched_t<TE, false, false, true>(s, b, all, steps, blocks,
                                                                         threads);
-        return with_form(false, all.stream, [&](auto form) {
+        return with_form(false, all.stream, threads, [&](auto form) {
             constexpr int FORM = decltype(form)::value;
             if constexpr (FORM != 16)
                 return kick ? launch_pass_batched_t<TE, true, false, false, FORM>(
                                   s, b, all, steps, blocks, threads)
-                            : launch_pass_batched_t<TE, false, false, false, FORM>(
+                            : launch_pass_batched_t<TE, false, false, false, FORM & 31>(
                                   s, b, all, steps, blocks, threads);
             return hipErrorInvalidValue;
         });
     }
-    return with_form(f.whole, all.stream && !f.six, [&](auto form) {
+    return with_form(f.whole, all.stream && !f.six, threads, [&](auto form) {
         constexpr int FORM = decltype(form)::value;
-        if constexpr (FORM != 8)
+        if constexpr (!(FORM & 8))
             if (f.six)
                 return kick ? launch_pass_batched_t<TE, true, true, true, FORM>(s, b, all, steps,
                                                                                 blocks, threads)

@@ -32,3 +32,23 @@ def test_back_to_the_automatic_size(gpu, n, nx):
             with pytest.raises(gpu.ScpicError) as e:
                 ctx.set_option(gpu.OPT_PASS_THREADS, threads)
             assert e.value.code == gpu.EINVAL
+
+
+# arrays above 128 MiB: the streamed form, in step with 1024 threads and ordered below
+@pytest.mark.parametrize("four_by_four", [False, True])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_streamed_sizes_give_the_same_bits(gpu, four_by_four, precision):
+    print(f"[case] streamed pass threads 4x4={four_by_four} {precision}", flush=True)
+    p = inputs.gaussian_beam(4_300_001, 3, 2e-3, 1e-3, 2e-3, 1e-3)
+    p["lost"][1000:70_000] = 1
+    lat = inputs.ring(4.2 / 4, 4.3 / 4, 2, 2e-8, four_by_four=four_by_four, k2l=5.0, sext_every=2)
+    ref = None
+    for threads in (0, 256, 512, 1024):
+        with gpu.Context(inputs.make_grid(128), precision) as ctx:
+            ctx.set_option(gpu.OPT_PASS_THREADS, threads)
+            d = gpu.to_device(p)
+            ctx.track(d, lat, 2)
+            got = gpu.to_host(d)
+        ref = ref or got
+        for k in p:
+            np.testing.assert_array_equal(got[k], ref[k], err_msg=f"{threads} {k}")
